@@ -14,9 +14,11 @@
 #include <vector>
 
 #include "../../include/sas_debye.h"
+#include "sas_bins.hpp"
 #include "sas_kernels.hpp"
 #include "sas_schedule.hpp"
 
+using sas::BinArgs;
 using sas::DescView;
 using sas::Geometry;
 using sas::StructDesc;
@@ -67,7 +69,7 @@ struct sas_ctx {
   // for one structure, the faster by timing in a plan, a grid for eager
   // batched calls), 1 persistent, 2 grid
   int launch = 0;
-  bool last_direct = false, last_per_atom = false, last_persist = false;
+  bool last_direct = false, last_per_atom = false, last_persist = false, last_bins = false;
   int32_t last_bj = 0, last_qc = 0;
   // pinned staging for the host-written blocks (descriptors of a batched
   // call, a non-uniform q grid, the orientation rule): a ring of slots, each
@@ -158,6 +160,8 @@ struct Schedule {
   bool per_atom = false;  // f_j inside the pair loop, no type sort
   bool persist = false;   // persistent pair-kernel launch with a work counter
   int32_t tg_types = 0;   // > 0: the forward also writes per-type table-gradient rows
+  bool bins = false;      // the binned form, with the forward kernel for what it leaves
+  BinArgs ba{};           // its sizes (no pointers)
   int32_t qc = 0, qc_template = 0;
   int32_t nchunks = 0, ldt = 0;  // q chunks; row stride of the padded table
   // adjoint (gradient) schedule, single structure only
@@ -178,6 +182,9 @@ struct Layout {
   size_t asum = 0;  // per-atom form: per pack block sums of f and f^2
   size_t gpart = 0, gslices = 0;  // table gradient: [strips][T][Nq], [slices][T][Nq]
   size_t counter = 0;             // persistent launch: the work counter
+  // binned form
+  size_t bxs = 0, bbox = 0, bnbins = 0, broute = 0, bpooloff = 0, bmeta = 0, bentries = 0, bpool = 0, bpart = 0,
+         bspart = 0;
   // host-written block, uploaded in one copy: structure descriptors (S > 1)
   // followed by the q grid (direct form)
   size_t upload = 0, upload_bytes = 0, desc = 0, qdev = 0;
@@ -323,6 +330,99 @@ Schedule make_schedule(const sas_ctx* ctx, const std::vector<int64_t>& sizes, in
   return sc;
 }
 
+// Time per unit, in pair*q steps of the type-form recurrence (measured on
+// MI355X): the per-pair set-up of the recurrence (about 66 steps), a step of
+// the direct form (4.3) and its set-up (5), and an atom*direction*q of the
+// orientation average with the rotation walk (6.5: whole calls on globules
+// gave 6.2 at 50,000 atoms and 7.6 at 20,000) or with a sine and cosine per q
+// (1.8x that, the kernels' ratio), plus a fixed cost of the averaged part
+// (the radius read back and the host's quadrature plan, about 0.1 ms, 2.2e9
+// steps), which keeps small molecules on the direct sum.
+constexpr double kSetupRecurrence = 66.0, kStepDirect = 4.3, kSetupDirect = 5.0, kCostOrient = 11.7,
+                 kCostOrientRot = 6.5, kCostOrientFixed = 2.2e9;
+
+// Steps the forward kernel runs for nq q values (chunks padded to templates).
+double direct_steps(int32_t nq, bool uniform) {
+  if (nq <= 0) return 0.0;
+  if (!uniform) return kSetupDirect + kStepDirect * 32.0 * ((nq + 31) / 32);
+  const int32_t nch = (nq + 199) / 200;
+  const int32_t qc = (nq + nch - 1) / nch;
+  return kSetupRecurrence * nch + static_cast<double>(nch) * pick_qc_template(qc, false);
+}
+
+// Whether a call takes the binned form, and its sizes.  It serves the type-sorted
+// form on any grid, unless the caller asked for the direct form or a tile shape
+// of the other kernels; small calls (few pairs or few q) stay with those.
+// qmax: the largest q (any positive value when only sizes are wanted).
+constexpr int64_t kBinPoolBytes = int64_t(512) << 20;  // most the sums of all bins may take
+constexpr int64_t kBinPoolHybrid = int64_t(1) << 20;   // the same in the hybrid's direct part
+constexpr int64_t kBinMinPairsEach = 8192;             // pairs per structure of a batch, on average
+constexpr int64_t kBinMaxAtoms = int64_t(1) << 21;     // (the 64-bit sums of a bin hold all its pairs)
+
+// max_pool: most bytes of bin sums (the hybrid's direct part keeps its
+// workspace small: a molecule that needs more goes to the other form).
+void add_bins(Schedule* sc, const sas_ctx* ctx, const std::vector<int64_t>& sizes, int32_t T, int32_t Nq, double qmax,
+              int64_t max_pool = kBinPoolBytes) {
+  sc->bins = false;
+  if (sc->per_atom || T > sas::kBinMaxTypes || Nq < sas::kBinMinNq || !(qmax > 0.0)) return;
+  if (ctx && (ctx->force_direct || ctx->force_bj > 0 || ctx->force_qc > 0)) return;
+  const int32_t TP = T * (T + 1) / 2;
+  const int64_t S = static_cast<int64_t>(sizes.size());
+  if (S <= 0 || S > (int64_t(1) << 24) / TP) return;
+  double pairs = 0.0;
+  for (int64_t n : sizes) {
+    if (n > kBinMaxAtoms) return;
+    pairs += 0.5 * static_cast<double>(n) * static_cast<double>(n - 1);
+  }
+  if (pairs < static_cast<double>(sas::kBinMinPairs) ||
+      pairs < static_cast<double>(kBinMinPairsEach) * static_cast<double>(S))
+    return;
+  BinArgs& b = sc->ba;
+  b = BinArgs{};
+  b.on = 1;
+  b.S = static_cast<int32_t>(S);
+  b.T = T;
+  b.TP = TP;
+  b.Nq = Nq;
+  b.invh = qmax / sas::kBinStep;
+  b.alt_steps = direct_steps(Nq, !sc->direct);
+  // items of 64 by 64 atoms, or shorter ones when those would leave CUs idle
+  const double tiles = pairs / (64.0 * 64.0);
+  b.sub = tiles >= 16384.0 ? 1 : (tiles >= 8192.0 ? 2 : (tiles >= 2048.0 ? 4 : 8));
+  // one work-group per CU, each with at least eight items: a smaller share costs
+  // more in emptying the bins than it saves
+  b.pair_wgs = static_cast<int32_t>(
+      std::max(1.0, std::min(static_cast<double>(ctx && ctx->cu_count > 0 ? ctx->cu_count : 256), tiles * b.sub / 8.0)));
+  // room for every bin count that pays, one structure at a time, within a bound
+  // (the plan leaves structures that do not fit to the other form)
+  int64_t pool = 0;
+  b.max_bins = sas::kBinCap * sas::kBinMaxWindows;
+  for (int64_t n : sizes) {
+    int64_t lo = sas::kBinFree, hi = b.max_bins;  // the largest count that pays
+    while (lo < hi) {
+      const int64_t mid = (lo + hi + 1) / 2;
+      if (sas::bin_pays(n, mid, TP, Nq, b.pair_wgs, b.alt_steps))
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    pool += lo * TP;
+  }
+  b.pool_cap = std::min<int64_t>(pool, max_pool / static_cast<int64_t>(8 * sas::kBinMoments));
+  const int64_t qgroups = (Nq + sas::kWave - 1) / sas::kWave;
+  b.wgs = static_cast<int32_t>(std::min<int64_t>(sas::kBinGroups, std::max<int64_t>(1, 512 / (S * qgroups))));
+  b.rows = b.wgs == 1 && sc->tg_types == 0 ? 1 : sas::kBinGroups;
+  sc->bins = true;
+}
+
+// make_schedule with the automatic shape, and the binned form where it serves.
+Schedule type_schedule(const sas_ctx* ctx, const std::vector<int64_t>& sizes, int32_t T, int32_t Nq, double qmax,
+                       bool direct, bool per_atom, int32_t tg_types = 0, int64_t max_pool = kBinPoolBytes) {
+  Schedule sc = make_schedule(ctx, sizes, T, Nq, 0, 0, direct, per_atom, tg_types);
+  add_bins(&sc, ctx, sizes, T, Nq, qmax, max_pool);
+  return sc;
+}
+
 // Tile shapes a plan may time: every J-block size, with the default q chunk
 // and with half of it (more waves per SIMD, but each chunk repeats the
 // per-pair FP64 set-up), each launched as a grid of one work-group per strip
@@ -440,7 +540,32 @@ Layout make_layout(const Schedule& sc, int32_t T, int32_t Nq) {
   // (the persistent launch's work counter; reserved for every schedule so that
   // the workspace queries do not depend on the launch form)
   L.counter = take(sizeof(unsigned long long));
-  L.partial = take(sizeof(double) * sc.n_strips * Nq);
+  // the pool of bin sums and the partial profiles of the binned form take the
+  // place of the strip rows where only one of them is in use (one structure)
+  const size_t rows = sizeof(double) * sc.n_strips * Nq;
+  if (sc.bins) {
+    const BinArgs& b = sc.ba;
+    L.bxs = take(sizeof(double) * 3 * (sc.n_total + sas::kBinPad));
+    L.bbox = take(sizeof(float) * 6 * sc.n_pack);
+    L.bnbins = take(sizeof(int32_t) * b.S);
+    L.broute = take(sizeof(int32_t) * b.S);
+    L.bpooloff = take(sizeof(int64_t) * b.S);
+    L.bmeta = take(sizeof(sas::BinMeta));
+    L.bentries = take(sizeof(sas::BinEntry) * (static_cast<size_t>(b.S) * b.TP + 1));
+    const size_t pool = align_up(sizeof(unsigned long long) * sas::kBinMoments * static_cast<size_t>(b.pool_cap));
+    const size_t part = align_up(sizeof(double) * static_cast<size_t>(b.S) * b.rows * Nq);
+    const size_t spart = sc.tg_types > 0 ? sizeof(double) * static_cast<size_t>(b.rows) * b.TP * Nq : 0;
+    if (b.S == 1) {
+      L.partial = L.bpool = take(std::max(rows, pool + part + spart));
+    } else {
+      L.bpool = take(pool + part + spart);
+      L.partial = take(rows);
+    }
+    L.bpart = L.bpool + pool;
+    L.bspart = L.bpart + part;
+  } else {
+    L.partial = take(rows);
+  }
   L.slices = take(sizeof(double) * sc.n_slices * Nq);
   if (sc.tg_types > 0) {
     L.gpart = take(sizeof(double) * sc.n_strips * static_cast<size_t>(sc.tg_types) * Nq);
@@ -477,6 +602,24 @@ sas_status check_offsets(const int64_t* offsets, int32_t S, std::vector<int64_t>
   }
   if (offsets[S] > (int64_t)INT32_MAX) return fail(SAS_ERR_UNSUPPORTED, "more than 2^31-1 atoms in total");
   return SAS_OK;
+}
+
+// The binned form's arguments with their pointers into the workspace.
+BinArgs bins_of(const Schedule& sc, void* ws, const Layout& L) {
+  BinArgs b = sc.ba;
+  char* w = static_cast<char*>(ws);
+  b.xs = reinterpret_cast<double*>(w + L.bxs);
+  b.toff = reinterpret_cast<const int32_t*>(w + L.toff);
+  b.bbox = reinterpret_cast<float*>(w + L.bbox);
+  b.nbins = reinterpret_cast<int32_t*>(w + L.bnbins);
+  b.route = reinterpret_cast<int32_t*>(w + L.broute);
+  b.pool_off = reinterpret_cast<int64_t*>(w + L.bpooloff);
+  b.meta = reinterpret_cast<sas::BinMeta*>(w + L.bmeta);
+  b.entries = reinterpret_cast<sas::BinEntry*>(w + L.bentries);
+  b.pool = reinterpret_cast<unsigned long long*>(w + L.bpool);
+  b.part = reinterpret_cast<double*>(w + L.bpart);
+  b.spart = sc.tg_types > 0 ? reinterpret_cast<double*>(w + L.bspart) : nullptr;
+  return b;
 }
 
 DescView view_of(const Schedule& sc, const void* ws, const Layout& L) {
@@ -592,8 +735,10 @@ sas_status stage_upload(sas_ctx* ctx, void* ws, const Layout& L, const std::vect
 
 // Record the form and tile shape a profile call used (sas_get_form, sas_get_variant).
 void note_last(sas_ctx* ctx, const Schedule& sc) {
-  ctx->last_bj = sc.geo.bj;
-  ctx->last_qc = sc.qc_template;
+  // (the binned form has no tile shape; 0, 0 asks for it again)
+  ctx->last_bj = sc.bins ? 0 : sc.geo.bj;
+  ctx->last_qc = sc.bins ? 0 : sc.qc_template;
+  ctx->last_bins = sc.bins;
   ctx->last_direct = sc.direct;
   ctx->last_per_atom = sc.per_atom;
   ctx->last_persist = sc.persist;
@@ -617,13 +762,19 @@ sas_status enqueue_forward(sas_ctx* ctx, const Schedule& sc, const Layout& L, co
   auto* slices = reinterpret_cast<double*>(w + L.slices);
   auto* tabp = reinterpret_cast<float*>(w + L.tabp);
   auto* asum = sc.per_atom ? reinterpret_cast<double*>(w + L.asum) : nullptr;
-  auto* counter = sc.persist ? reinterpret_cast<unsigned long long*>(w + L.counter) : nullptr;
-  SAS_HIP(sas::launch_pad_table(table, T, Nq, sc.ldt, tabp, st, counter));
+  // (behind the binned form the forward kernel usually has nothing to do, which
+  // a persistent grid finds out soonest)
+  const bool persist = sc.persist || (sc.bins && sc.tg_types == 0);
+  auto* counter = persist ? reinterpret_cast<unsigned long long*>(w + L.counter) : nullptr;
+  BinArgs bins{};
+  if (sc.bins) bins = bins_of(sc, ws, L);
   if (sc.per_atom) {
+    SAS_HIP(sas::launch_pad_table(table, T, Nq, sc.ldt, tabp, st, counter));
     SAS_HIP(sas::launch_pack_plain(coords, types, sc.n_total, T, xyz, tsort, perm, st));
     SAS_HIP(sas::launch_atom_sums(sd, sc.n_pack, tsort, tabp, T, sc.ldt, Nq, asum, st));
   } else {
-    SAS_HIP(sas::launch_pack(coords, types, sd, sc.S, sc.n_pack, T, bcount, toff, xyz, tsort, perm, st));
+    SAS_HIP(sas::launch_pack(coords, types, sd, sc.S, sc.n_pack, T, bcount, toff, xyz, tsort, perm, table, Nq, sc.ldt,
+                             tabp, counter, sc.bins ? &bins : nullptr, st));
   }
   sas::ForwardArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -644,8 +795,13 @@ sas_status enqueue_forward(sas_ctx* ctx, const Schedule& sc, const Layout& L, co
   a.gpart = sc.tg_types > 0 ? reinterpret_cast<double*>(w + L.gpart) : nullptr;
   a.counter = counter;
   a.n_work = sc.n_strips * sc.nchunks;
+  if (sc.bins) {
+    a.route = bins.route;
+    a.fallback = &bins.meta->fallback;
+  }
   {
     LaunchTimer timer(ctx, st, false);
+    if (sc.bins) SAS_HIP(sas::launch_bins(bins, st));
     if (sc.per_atom)
       SAS_HIP(sas::launch_forward_pa(a, sc.n_strips, sc.qc_template, st));
     else if (sc.tg_types > 0)
@@ -653,7 +809,9 @@ sas_status enqueue_forward(sas_ctx* ctx, const Schedule& sc, const Layout& L, co
     else
       SAS_HIP(sas::launch_forward(a, sc.n_strips, sc.qc_template, st));
   }
-  if (I_out)
+  if (sc.bins)
+    SAS_HIP(sas::launch_bins_reduce(bins, sd, sc.n_slices, partial, slices, toff, table, Nq, q0, dq, qdev, I_out, st));
+  else if (I_out)
     SAS_HIP(sas::launch_reduce(sd, sc.S, sc.n_slices, partial, slices, sc.per_atom ? nullptr : toff, asum, table, T,
                                Nq, q0, dq, qdev, I_out, st));
   return SAS_OK;
@@ -982,7 +1140,7 @@ size_t sas_debye_workspace_size(const sas_ctx* ctx, int64_t n, int32_t t, int32_
     for (bool direct : {false, true})
       need = std::max(need, table_grad_by_atom(ctx, t)
                                 ? rows_layout(ctx, n, t, nq, direct).total
-                                : make_layout(make_schedule(ctx, sizes, t, nq, 0, 0, direct, false, t), t, nq).total);
+                                : make_layout(type_schedule(ctx, sizes, t, nq, 1.0, direct, false, t), t, nq).total);
     return need;
   }
   if (grad) {
@@ -991,7 +1149,7 @@ size_t sas_debye_workspace_size(const sas_ctx* ctx, int64_t n, int32_t t, int32_
     const bool pa = use_per_atom(ctx, t, n);
     size_t need = 0;
     for (bool direct : {false, true}) {
-      Schedule sc = make_schedule(ctx, sizes, t, nq, 0, 0, direct, pa);
+      Schedule sc = type_schedule(ctx, sizes, t, nq, 1.0, direct, pa);
       if (pa)
         add_adjoint_pa(&sc, n, nq);
       else
@@ -1004,7 +1162,7 @@ size_t sas_debye_workspace_size(const sas_ctx* ctx, int64_t n, int32_t t, int32_
   const bool pa = use_per_atom(ctx, t, n);
   size_t need = 0;
   for (bool direct : {false, true})
-    need = std::max(need, make_layout(make_schedule(ctx, sizes, t, nq, 0, 0, direct, pa), t, nq).total);
+    need = std::max(need, make_layout(type_schedule(ctx, sizes, t, nq, 1.0, direct, pa), t, nq).total);
   return need;
 }
 
@@ -1019,7 +1177,7 @@ sas_status sas_debye_profile(sas_ctx* ctx, const float* coords, const int32_t* t
   QGrid grid;
   st = classify_q(q, nq, &grid);
   if (st != SAS_OK) return st;
-  const Schedule sc = make_schedule(ctx, std::vector<int64_t>{n}, t, nq, 0, 0, !grid.uniform || ctx->force_direct,
+  const Schedule sc = type_schedule(ctx, std::vector<int64_t>{n}, t, nq, q[nq - 1], !grid.uniform || ctx->force_direct,
                                     use_per_atom(ctx, t, n));
   const Layout L = make_layout(sc, t, nq);
   if (!workspace) return fail(SAS_ERR_INVALID_ARG, "workspace is NULL");
@@ -1067,6 +1225,22 @@ sas_status sas_debye_profile_noalloc(sas_ctx* ctx, const float* coords, const in
     return fail(SAS_ERR_UNSUPPORTED, "n = %lld, t = %d, nq = %d needs %zu bytes of scratch; the allocation-free "
                 "call has %zu (use sas_debye_profile with a workspace)", (long long)n, t, nq, L.total,
                 (size_t)SAS_NOALLOC_SCRATCH_BYTES);
+  // the binned form where its extra scratch fits too (with a smaller pool of
+  // bin sums if need be: a molecule that outgrows it is left to the recurrence)
+  {
+    Schedule sb = sc;
+    add_bins(&sb, ctx, std::vector<int64_t>{n}, t, nq, q[nq - 1]);
+    while (sb.bins) {
+      const Layout Lb = make_layout(sb, t, nq);
+      if (Lb.total <= SAS_NOALLOC_SCRATCH_BYTES) {
+        sc = sb;
+        L = Lb;
+        break;
+      }
+      sb.ba.pool_cap /= 2;
+      if (sb.ba.pool_cap < 512LL * sb.ba.TP) break;
+    }
+  }
   if (!ctx->scratch) return fail(SAS_ERR_HIP, "no scratch address for device %d", ctx->device);
   DeviceGuard g(ctx->device);
   if (!g.ok) return fail(SAS_ERR_HIP, "hipSetDevice(%d) failed", ctx->device);
@@ -1088,7 +1262,9 @@ size_t sas_debye_workspace_size_batched(const sas_ctx* ctx, const int64_t* offse
   // large enough for the automatic shape, every shape a plan may time, and
   // the direct form (the grid is not known here)
   const bool pa = use_per_atom(ctx, t, max_size(sizes));
-  size_t need = make_layout(make_schedule(ctx, sizes, t, nq, 0, 0, false, pa), t, nq).total;
+  size_t need = 0;
+  for (bool direct : {false, true})
+    need = std::max(need, make_layout(type_schedule(ctx, sizes, t, nq, 1.0, direct, pa), t, nq).total);
   for (bool direct : {false, true})
     for (const auto& c : tile_candidates(ctx, nq, direct, pa))
       need = std::max(need, make_layout(make_schedule(ctx, sizes, t, nq, c.bj, c.qc, direct, pa, 0, c.persist ? 1 : 0),
@@ -1112,7 +1288,7 @@ sas_status sas_debye_profile_batched(sas_ctx* ctx, const float* coords, const in
   st = classify_q(q, nq, &grid);
   if (st != SAS_OK) return st;
   if (S == 0) return SAS_OK;
-  const Schedule sc = make_schedule(ctx, sizes, t, nq, 0, 0, !grid.uniform || ctx->force_direct,
+  const Schedule sc = type_schedule(ctx, sizes, t, nq, q[nq - 1], !grid.uniform || ctx->force_direct,
                                     use_per_atom(ctx, t, max_size(sizes)));
   const Layout L = make_layout(sc, t, nq);
   if (!workspace) return fail(SAS_ERR_INVALID_ARG, "workspace is NULL");
@@ -1237,7 +1413,7 @@ sas_status sas_plan_create_batched(sas_ctx* ctx, const float* coords, const int3
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign) return fail(SAS_ERR_INVALID_ARG, "workspace not 256-byte aligned");
   const bool direct = !grid.uniform || ctx->force_direct;
   const bool per_atom = use_per_atom(ctx, t, max_size(sizes));
-  const Schedule sc0 = make_schedule(ctx, sizes, t, nq, 0, 0, direct, per_atom);
+  const Schedule sc0 = type_schedule(ctx, sizes, t, nq, q[nq - 1], direct, per_atom);
   const size_t need = make_layout(sc0, t, nq).total;
   if (ws_bytes < need) return fail(SAS_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes, need %zu", ws_bytes, need);
   sas_plan* p = new (std::nothrow) sas_plan();
@@ -1273,13 +1449,16 @@ sas_status sas_plan_execute(sas_plan* p, void* stream) {
     if (sv != SAS_OK) return sv;
   }
   if (!p->ready) {
-    // choose the tile shape: forced variant, cached choice, or timing
+    // the binned form has no shape to choose; otherwise choose the tile shape:
+    // forced variant, cached choice, or timing
+    p->sc = type_schedule(p->ctx, p->sizes, p->T, p->Nq, p->qh.back(), p->direct, p->per_atom);
     sas_ctx::Tile tile;
     const std::string key = workload_key(p->sizes, p->T, p->Nq) + (p->direct ? "d" : "u") + (p->per_atom ? "a" : "t") +
                             (p->ctx->launch == 1 ? "p" : (p->ctx->launch == 2 ? "g" : ""));
     const bool forced = p->ctx->force_bj > 0 || p->ctx->force_qc > 0;
     auto it = p->ctx->tuned.find(key);
-    if (forced) {
+    if (p->sc.bins) {
+    } else if (forced) {
       tile.bj = p->ctx->force_bj;
       tile.persist = p->ctx->launch != 2 && !p->direct && !p->per_atom;
     } else if (it != p->ctx->tuned.end()) {
@@ -1289,8 +1468,9 @@ sas_status sas_plan_execute(sas_plan* p, void* stream) {
       if (st != SAS_OK) return st;
       p->ctx->tuned[key] = tile;
     }
-    p->sc = make_schedule(p->ctx, p->sizes, p->T, p->Nq, tile.bj, tile.qc, p->direct, p->per_atom, 0,
-                          tile.persist ? 1 : 0);
+    if (!p->sc.bins)
+      p->sc = make_schedule(p->ctx, p->sizes, p->T, p->Nq, tile.bj, tile.qc, p->direct, p->per_atom, 0,
+                            tile.persist ? 1 : 0);
     p->L = make_layout(p->sc, p->T, p->Nq);
     if (p->L.total > p->ws_bytes)
       return fail(SAS_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes, need %zu", p->ws_bytes, p->L.total);
@@ -1360,7 +1540,7 @@ sas_status sas_debye_grad_table(sas_ctx* ctx, const float* coords, const int32_t
     }
     return st;
   }
-  const Schedule sc = make_schedule(ctx, std::vector<int64_t>{n}, t, nq, 0, 0, !grid.uniform || ctx->force_direct,
+  const Schedule sc = type_schedule(ctx, std::vector<int64_t>{n}, t, nq, q[nq - 1], !grid.uniform || ctx->force_direct,
                                     false, t);
   const Layout L = make_layout(sc, t, nq);
   if (!workspace) return fail(SAS_ERR_INVALID_ARG, "workspace is NULL");
@@ -1379,10 +1559,11 @@ sas_status sas_debye_grad_table(sas_ctx* ctx, const float* coords, const int32_t
   if (st != SAS_OK) return st;
   const double* qdev = sc.direct ? reinterpret_cast<const double*>(w + L.qdev) : nullptr;
   auto* gslices = reinterpret_cast<double*>(w + L.gslices);
+  const BinArgs bins = sc.bins ? bins_of(sc, workspace, L) : BinArgs{};
   SAS_HIP(sas::launch_reduce_slices(view_of(sc, workspace, L), sc.n_slices, reinterpret_cast<const double*>(w + L.gpart),
-                                    t * nq, gslices, hs));
+                                    t * nq, gslices, sc.bins ? &bins.meta->fallback : nullptr, hs));
   SAS_HIP(sas::launch_table_grad_final(sc.n_slices, gslices, reinterpret_cast<const int32_t*>(w + L.toff), table, t, nq,
-                                       grid.q0, grid.dq, qdev, dL_dI, grad_table_out, hs));
+                                       grid.q0, grid.dq, qdev, dL_dI, sc.bins ? &bins : nullptr, grad_table_out, hs));
   note_last(ctx, sc);
   return SAS_OK;
 }
@@ -1403,7 +1584,7 @@ sas_status sas_debye_grad(sas_ctx* ctx, const float* coords, const int32_t* type
   // of the forward and the adjoint; many table rows (or a forced per-atom
   // form) the per-atom ones
   const bool pa = use_per_atom(ctx, t, n);
-  Schedule sc = make_schedule(ctx, std::vector<int64_t>{n}, t, nq, 0, 0, !grid.uniform || ctx->force_direct, pa);
+  Schedule sc = type_schedule(ctx, std::vector<int64_t>{n}, t, nq, q[nq - 1], !grid.uniform || ctx->force_direct, pa);
   if (pa)
     add_adjoint_pa(&sc, n, nq);
   else
@@ -1425,16 +1606,18 @@ sas_status sas_debye_grad(sas_ctx* ctx, const float* coords, const int32_t* type
     st = enqueue_forward(ctx, sc, L, coords, types, table, t, nq, q0, dq, I_out, workspace, hs);
     if (st != SAS_OK) return st;
   } else {
-    SAS_HIP(sas::launch_pad_table(table, t, nq, sc.ldt, reinterpret_cast<float*>(w + L.tabp), hs));
-    if (pa)
+    auto* tabp = reinterpret_cast<float*>(w + L.tabp);
+    if (pa) {
+      SAS_HIP(sas::launch_pad_table(table, t, nq, sc.ldt, tabp, hs));
       SAS_HIP(sas::launch_pack_plain(coords, types, n, t, reinterpret_cast<double4*>(w + L.xyz),
                                      reinterpret_cast<int32_t*>(w + L.tsort), reinterpret_cast<int32_t*>(w + L.perm),
                                      hs));
-    else
+    } else {
       SAS_HIP(sas::launch_pack(coords, types, view_of(sc, workspace, L), sc.S, sc.n_pack, t,
                                reinterpret_cast<int32_t*>(w + L.bcount), reinterpret_cast<int32_t*>(w + L.toff),
                                reinterpret_cast<double4*>(w + L.xyz), reinterpret_cast<int32_t*>(w + L.tsort),
-                               reinterpret_cast<int32_t*>(w + L.perm), hs));
+                               reinterpret_cast<int32_t*>(w + L.perm), table, nq, sc.ldt, tabp, nullptr, nullptr, hs));
+    }
   }
   if (n == 0) return SAS_OK;
   sas::AdjArgs a;
@@ -1478,17 +1661,6 @@ namespace {
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr int64_t kOrientCapAll = int64_t(1) << 17;  // directions per chunk when every q is averaged
 constexpr int64_t kOrientBlocksTarget = 16384;         // most work-groups the amplitude kernel takes
-// Time per unit, in pair*q steps of the type-form recurrence (measured on
-// MI355X): the per-pair set-up of the recurrence (about 66 steps), a step of
-// the direct form (4.3) and its set-up (5), and an atom*direction*q of the
-// orientation average with the rotation walk (6.5: whole calls on globules
-// gave 6.2 at 50,000 atoms and 7.6 at 20,000) or with a sine and cosine per q
-// (1.8x that, the kernels' ratio), plus a fixed cost of the averaged part
-// (the radius read back and the host's quadrature plan, about 0.1 ms, 2.2e9
-// steps), which keeps small molecules on the direct sum.
-constexpr double kSetupRecurrence = 66.0, kStepDirect = 4.3, kSetupDirect = 5.0, kCostOrient = 11.7,
-                 kCostOrientRot = 6.5, kCostOrientFixed = 2.2e9;
-
 // The orientation kernel walks exp(i q p) over the leading nq_o q values when
 // they form a uniform grid whose step *dq turns the farthest atom's phase by
 // at most kRotMaxStep.
@@ -1498,15 +1670,6 @@ bool orient_rot(const double* q, int32_t nq_o, double r_max, double* dq) {
   if (!(g.dq * r_max <= sas::kRotMaxStep)) return false;
   if (dq) *dq = g.dq;
   return true;
-}
-
-// Steps the forward kernel runs for nq q values (chunks padded to templates).
-double direct_steps(int32_t nq, bool uniform) {
-  if (nq <= 0) return 0.0;
-  if (!uniform) return kSetupDirect + kStepDirect * 32.0 * ((nq + 31) / 32);
-  const int32_t nch = (nq + 199) / 200;
-  const int32_t qc = (nq + nch - 1) / nch;
-  return kSetupRecurrence * nch + static_cast<double>(nch) * pick_qc_template(qc, false);
 }
 
 // Gauss-Legendre rule of n points on [-1, 1]: roots of P_n by Newton's method
@@ -1661,7 +1824,7 @@ size_t direct_part_bytes(const sas_ctx* ctx, int64_t n, int32_t t, int32_t nq_d)
   const bool pa = use_per_atom(ctx, t, n);
   size_t need = 0;
   for (bool direct : {false, true})
-    need = std::max(need, make_layout(make_schedule(ctx, sizes, t, nq_d, 0, 0, direct, pa), t, nq_d).total);
+    need = std::max(need, make_layout(type_schedule(ctx, sizes, t, nq_d, 1.0, direct, pa, 0, kBinPoolHybrid), t, nq_d).total);
   return need;
 }
 
@@ -1868,8 +2031,8 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     if (st != SAS_OK) return st;
     float* tabd = reinterpret_cast<float*>(w + L.tabd);
     SAS_HIP(sas::launch_copy_cols(table, t, nq, nq_o, nq_d, nq_d, tabd, hd));
-    const Schedule sd = make_schedule(ctx, std::vector<int64_t>{n}, t, nq_d, 0, 0, !gd.uniform || ctx->force_direct,
-                                      use_per_atom(ctx, t, n));
+    const Schedule sd = type_schedule(ctx, std::vector<int64_t>{n}, t, nq_d, q[nq - 1], !gd.uniform || ctx->force_direct,
+                                      use_per_atom(ctx, t, n), 0, kBinPoolHybrid);
     const Layout Ld = make_layout(sd, t, nq_d);
     void* wd = w + L.direct;
     st = stage_upload(ctx, wd, Ld, upload_image(sd, Ld, gd), hd);

@@ -1,0 +1,131 @@
+// The binned form of the type-sorted sums (sas_bins.hip): interface and the
+// rules shared by its kernels and the host.
+//
+// Every pair's distance is formed in FP64, as in the other forms, but instead
+// of meeting each q the pair is deposited once, as powers of its position
+// inside a narrow bin of the squared distance.  With t = r qmax / kBinStep,
+// bin b holds t in [b, b + 1) and the pair's coordinate is
+//     u = (t^2 - (b + 1/2)^2) / (b + 1/2),  about [-1, 1].
+// Per type pair and bin the sums of u^k, k = 0..5, fix the sum over the bin's
+// pairs of any function of r^2 that a polynomial of degree 5 in u represents
+// over the bin; sinc(q r) is an entire function of r^2 and q r moves by at most
+// kBinStep across a bin, so its interpolation at six Gauss-Legendre nodes is
+// off by at most 3e-8 of a pair's term at the largest q and by (q/qmax)^6 of
+// that at the others.  The cost of a pair is then the same for 10 q values as
+// for 200, on any grid.
+//
+// The sums are exact integers (fixed point), so they do not depend on the
+// order of the pairs: results are deterministic, and a structure's are the
+// same in a batch as alone.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "sas_kernels.hpp"
+
+namespace sas {
+
+constexpr int kBinMoments = 6;        // sums of u^0 .. u^5
+constexpr double kBinStep = 0.52;     // q r per bin at the largest q: a 3,500 A molecule at q = 1 fits one window
+constexpr int kBinCap = 6592;         // bins of one LDS window (24 bytes each: 154.5 KiB of the 160)
+constexpr int kBinMaxWindows = 4;     // windows a distance range may take before the other forms are cheaper
+constexpr int kBinMaxTypes = 64;      // T (type pairs: T (T + 1) / 2)
+constexpr int kBinThreads = 1024;     // one work-group per CU
+constexpr int kBinWaves = kBinThreads / kWave;
+constexpr int kBinPad = 8;            // rows past the last atom that a batch may read
+constexpr int kBinSegs = 64;          // (structure, type pair) sums a work-group keeps at a time
+constexpr int kBinChunk = 8;          // bins turned into nodes at a time by the final sums
+
+// One (structure, type pair): rows of the two type segments (lane side a, swept
+// side b), its first work item and its sums' place in the pool.
+struct BinEntry {
+  int64_t item0;   // first item; items run to the next entry's item0
+  int64_t pool;    // first bin in the pool
+  int32_t a0, na;  // absolute sorted rows held by the lanes
+  int32_t b0, nb;  // absolute sorted rows swept
+  int32_t nbins;
+  int32_t base;    // items of one window
+  int32_t diag;    // both segments are one type: pairs j > i only
+  int32_t pad;
+};
+
+// Device-side results of the planning step.
+struct BinMeta {
+  int64_t items;      // total work items
+  int64_t pool_used;  // bins in use
+  int32_t fallback;   // structures left to the recurrence or direct form
+  int32_t pad;
+};
+
+struct BinArgs {
+  int32_t on;              // 0: this call does not use the binned form
+  int32_t S, T, TP;        // structures, types, type pairs
+  int32_t sub;             // items per 64-atom tile of the swept side (1, 2, 4 or 8)
+  int32_t max_bins;        // bins a structure may take (windows included)
+  int64_t pool_cap;        // bins the pool holds
+  double invh;             // qmax / kBinStep
+  double* xs;              // [atoms + kBinPad][3] sorted coordinates times invh
+  const int32_t* toff;     // [S][T + 1] absolute start of each type segment
+  float* bbox;             // [pack blocks][6] lower and upper corners
+  int32_t* nbins;          // [S]
+  int32_t* route;          // [S] 1: binned, 0: left to the other form
+  int64_t* pool_off;       // [S]
+  BinMeta* meta;
+  BinEntry* entries;       // [S * TP + 1]
+  unsigned long long* pool;  // [bins][kBinMoments], fixed point
+  double* part;            // [S][rows][Nq] partial profiles
+  double* spart;           // table gradient: [rows][TP][Nq] partial sums per type pair
+  int32_t wgs;             // work-groups per structure and 64 q in the final sums
+  int32_t rows;            // rows of part and spart: 1 for one work-group (which adds its groups), else kBinGroups
+  int32_t Nq;
+  int32_t pair_wgs;        // work-groups of the pair kernel
+  double alt_steps;        // steps per pair of the form it replaces
+};
+
+// Fixed point.  A pair adds three 64-bit words per bin: count | u, u^5 | u^2,
+// u^4 | u^3.  Each power enters as the bits of fma(u^k, 2^bits, 1.5 2^23),
+// whose low 23 bits hold it rounded to nearest; the constant bits are taken
+// out again with the count.  The bits leave each field room for kBinMaxCount
+// pairs of one bin.
+constexpr int kBinBits1 = 21, kBinBits2 = 17, kBinBits3 = 14, kBinBits4 = 10, kBinBits5 = 7;
+constexpr int kBinShift5 = 4, kBinShift4 = 2;  // left shifts of the upper fields
+constexpr int kBinCountShift = 10;             // the count's place in the upper half of the first word
+constexpr uint32_t kBinMagicBits = 0x4b400000u;
+constexpr int kBinSpill = 1 << 15;             // bins this full are emptied between rounds
+constexpr int kBinMaxCount = kBinSpill + kBinWaves * kWave * 64;
+
+// The type form's profile of n atoms is binned from this many pairs (measured
+// on MI355X) and q values.
+constexpr int64_t kBinMinPairs = 73536;
+constexpr int32_t kBinMinNq = 8;
+
+// Estimated times in ns of the binned form and of the form it replaces, from
+// whole calls measured on MI355X: per pair and window (the rod, 1.25e9 pairs in
+// 1.8 ms), per bin and q of the final sums, and per bin and pass of emptying
+// the bins; against steps of the recurrence at 5.2e-5 (alt_steps per pair).
+constexpr double kBinPairNs = 1.5e-3, kBinNodeNs = 1e-2, kBinFlushNs = 4e-2, kBinStepNs = 5.2e-5;
+constexpr int kBinFree = 512;  // bins that are always taken
+
+// Whether a structure of n atoms that spans nbins bins is binned.
+__host__ __device__ inline bool bin_pays(int64_t n, int64_t nbins, int32_t TP, int32_t Nq, int32_t wgs,
+                                         double alt_steps) {
+  if (nbins <= kBinFree) return true;
+  const double pairs = 0.5 * static_cast<double>(n) * static_cast<double>(n - 1);
+  const double windows = static_cast<double>((nbins + kBinCap - 1) / kBinCap);
+  const double passes = static_cast<double>(wgs + TP);
+  const double binned = pairs * windows * kBinPairNs + static_cast<double>(nbins) * (kBinNodeNs * Nq + kBinFlushNs * passes);
+  return binned < pairs * alt_steps * kBinStepNs;
+}
+
+// Groups the final sums of a structure are cut into (chunk c of bins belongs to
+// group c mod kBinGroups); their totals are added in order.
+constexpr int kBinGroups = 64;
+
+hipError_t launch_bins_plan(const BinArgs& b, const DescView& sd, const int32_t* toff, hipStream_t st);
+hipError_t launch_bins(const BinArgs& b, hipStream_t st);
+// The final sums of the binned structures, and the slice sums of the others.
+hipError_t launch_bins_reduce(const BinArgs& b, const DescView& sd, int64_t n_slices, const double* partial,
+                              double* slices, const int32_t* toff, const float* table, int32_t Nq, double q0, double dq,
+                              const double* qdev, double* I_out, hipStream_t st);
+
+}  // namespace sas

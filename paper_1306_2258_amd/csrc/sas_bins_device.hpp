@@ -1,0 +1,171 @@
+// Device pieces of the binned form shared by the pack (planning), the bins and
+// the final sums.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "sas_bins.hpp"
+#include "sas_kernels.hpp"
+
+namespace sas {
+
+// Index k = j (j + 1) / 2 + i of the pair i <= j.
+__device__ __forceinline__ void tri_decode(int k, int* i, int* j) {
+  int y = static_cast<int>((__fsqrt_rn(8.f * static_cast<float>(k) + 1.f) - 1.f) * 0.5f);
+  while (static_cast<int64_t>(y + 1) * (y + 2) / 2 <= k) ++y;
+  while (static_cast<int64_t>(y) * (y + 1) / 2 > k) --y;
+  *j = y;
+  *i = k - static_cast<int>(static_cast<int64_t>(y) * (y + 1) / 2);
+}
+
+// Bins of a structure of n atoms whose bounding box has the diagonal `diag`
+// in Angstrom; 0 when the other form is faster (or a coordinate is not
+// finite).  The margin covers the FP32 root that picks a pair's bin.
+__device__ __forceinline__ int32_t bin_count(const BinArgs& b, double diag, int32_t n) {
+  const double t = diag * b.invh * (1.0 + 1e-6);
+  if (!(t < static_cast<double>(b.max_bins - 2))) return 0;
+  const int32_t nbins = static_cast<int32_t>(t) + 2;
+  return bin_pays(n, nbins, b.TP, b.Nq, b.pair_wgs, b.alt_steps) ? nbins : 0;
+}
+
+// Place of atom d of a type segment of n in the binned form's order.  Neighbours
+// in the caller's order are often neighbours in space; 64 of them against one
+// atom would fall into few bins and their atomics into line.  So the lanes of a
+// wave take atoms n/64 apart: the segment, as rows of ceil(n/64), is read by
+// columns.
+__device__ __forceinline__ int32_t bin_spread(int32_t d, int32_t n) {
+  const int32_t m = (n + kWave - 1) / kWave, r = (n + m - 1) / m;  // row length, rows
+  const int32_t full = n - (r - 1) * m;                            // columns of r atoms; the rest have r - 1
+  const int32_t row = d / m, col = d - row * m;
+  return col < full ? col * r + row : full * r + (col - full) * (r - 1) + row;
+}
+
+// Rows of partial profiles a structure's final sums write.
+__device__ __forceinline__ int bin_rows(const BinArgs& b, int32_t nbins) {
+  return min(b.rows, (nbins + kBinChunk - 1) / kBinChunk);
+}
+
+// Inclusive scan of v over the 256 threads of a work-group; *sum is the total.
+__device__ __forceinline__ int64_t scan256(int64_t v, int64_t* sum) {
+  __shared__ int64_t tot[4];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int64_t y = __shfl_up(v, off, kWave);
+    if (lane >= off) v += y;
+  }
+  __syncthreads();
+  if (lane == kWave - 1) tot[w] = v;
+  __syncthreads();
+  for (int k = 0; k < w; ++k) v += tot[k];
+  *sum = tot[0] + tot[1] + tot[2] + tot[3];
+  return v;
+}
+
+// Planning by one work-group of 256 threads, after b.nbins (bins per
+// structure, 0: too many) and the type segments toff are known.
+__device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int32_t* toff) {
+  __shared__ int32_t fallback;
+  if (threadIdx.x == 0) fallback = 0;
+  __syncthreads();
+  int64_t pool = 0;
+  for (int s0 = 0; s0 < b.S; s0 += 256) {
+    const int s = s0 + threadIdx.x;
+    const int32_t nb = s < b.S ? b.nbins[s] : 0;
+    const int64_t want = static_cast<int64_t>(nb) * b.TP;
+    int64_t sum = 0;
+    const int64_t incl = scan256(want, &sum);
+    if (s < b.S) {
+      const int64_t off = pool + incl - want;
+      const bool ok = nb > 0 && off + want <= b.pool_cap;
+      b.pool_off[s] = ok ? off : 0;
+      b.route[s] = ok ? 1 : 0;
+      if (!ok) atomicAdd(&fallback, 1);
+    }
+    pool += sum;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    b.meta->pool_used = pool < b.pool_cap ? pool : b.pool_cap;
+    b.meta->fallback = fallback;
+  }
+  const int E = b.S * b.TP;
+  int64_t items = 0;
+  for (int x0 = 0; x0 < E; x0 += 256) {
+    const int x = x0 + threadIdx.x;
+    BinEntry en{};
+    int64_t count = 0;
+    if (x < E) {
+      const int s = x / b.TP;
+      int ta, tb;
+      tri_decode(x - s * b.TP, &ta, &tb);
+      const int32_t* o = toff + static_cast<int64_t>(s) * (b.T + 1);
+      en.a0 = o[ta];
+      en.na = o[ta + 1] - o[ta];
+      en.b0 = o[tb];
+      en.nb = o[tb + 1] - o[tb];
+      en.diag = ta == tb;
+      // (the side that fills the lanes better is held by them)
+      const int64_t ia = (en.na + kWave - 1) / kWave, ib = (en.nb + kWave - 1) / kWave;
+      if (ib * en.na < ia * en.nb) {
+        const int32_t a0 = en.a0, na = en.na;
+        en.a0 = en.b0;
+        en.na = en.nb;
+        en.b0 = a0;
+        en.nb = na;
+      }
+      en.nbins = b.nbins[s];
+      en.pool = b.pool_off[s] + static_cast<int64_t>(x - s * b.TP) * en.nbins;
+      const int64_t tiles = en.diag ? ia * (ia + 1) / 2 : ia * ib;
+      en.base = static_cast<int32_t>(tiles * b.sub);
+      const int wins = (en.nbins + kBinCap - 1) / kBinCap;
+      const bool any = b.route[s] && en.na > 0 && en.nb > 0 && !(en.diag && en.na < 2);
+      count = any ? static_cast<int64_t>(en.base) * wins : 0;
+    }
+    int64_t sum = 0;
+    const int64_t incl = scan256(count, &sum);
+    if (x < E) {
+      en.item0 = items + incl - count;
+      b.entries[x] = en;
+    }
+    items += sum;
+  }
+  if (threadIdx.x == 0) {
+    BinEntry end{};
+    end.item0 = items;
+    b.entries[E] = end;
+    b.meta->items = items;
+  }
+}
+
+// Centre and half width of bin b in t^2 are b^2 + b + 1/2 and b + 1/2: the
+// radius (in units of 1 / invh) of the node at v in [-1, 1].
+__device__ __forceinline__ double bin_node_radius(int bin, double v) {
+  const double c = bin + 0.5;
+  return sqrt(static_cast<double>(bin) * bin + c + c * v);
+}
+
+// Weights of a bin's six nodes from its integer sums: the sums of u^k, moved to
+// the powers of v = u - 1/(4 (b + 1/2)), which spans [-1, 1] over the bin.
+__device__ __forceinline__ void bin_node_weights(const unsigned long long (&p)[kBinMoments], int bin,
+                                                 const double (&L)[kBinMoments][kBinMoments],
+                                                 double (&wn)[kBinMoments]) {
+  constexpr int kBits[kBinMoments] = {0, kBinBits1, kBinBits2, kBinBits3, kBinBits4, kBinBits5};
+  double m[kBinMoments];
+#pragma unroll
+  for (int k = 0; k < kBinMoments; ++k)
+    m[k] = static_cast<double>(static_cast<long long>(p[k])) / static_cast<double>(1ll << kBits[k]);
+  const double al = -0.25 / (bin + 0.5);
+  // sums of (u + al)^k by repeated Horner shifts: m_k += al m_{k-1}, from the top
+#pragma unroll
+  for (int pass = 1; pass < kBinMoments; ++pass)
+#pragma unroll
+    for (int k = kBinMoments - 1; k >= pass; --k) m[k] = fma(al, m[k - 1], m[k]);
+#pragma unroll
+  for (int j = 0; j < kBinMoments; ++j) {
+    double w = 0.0;
+#pragma unroll
+    for (int k = 0; k < kBinMoments; ++k) w = fma(m[k], L[k][j], w);
+    wn[j] = w;
+  }
+}
+
+}  // namespace sas

@@ -32,6 +32,7 @@ __device__ __forceinline__ void forward_strip(const ForwardArgs& a, int64_t t, i
   constexpr int NT = NG + (R ? 1 : 0);    // q values owned per lane after the lane reduction
   __shared__ double4 sj[BJ];
   const int s = find_struct_by_strip(a.sd, t);
+  if (a.route && a.route[s]) return;  // (binned)
   const StructDesc d = a.sd.get(s);
   const StripPos sp = decode_strip(t - d.strip_off, d.n, a.geo);
   const int n = d.n;
@@ -306,6 +307,7 @@ __device__ __forceinline__ void forward_strip(const ForwardArgs& a, int64_t t, i
 // One work-group per (strip, q chunk): blockIdx.x is the strip, blockIdx.y the chunk.
 template <int QC, int BJ, bool DIRECT, bool TG>
 __global__ __launch_bounds__(kWave, forward_waves(QC, BJ, DIRECT)) void k_forward(ForwardArgs a) {
+  if (a.fallback && *a.fallback == 0) return;
   forward_strip<QC, BJ, DIRECT, TG>(a, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
@@ -315,8 +317,9 @@ __global__ __launch_bounds__(kWave, forward_waves(QC, BJ, DIRECT)) void k_forwar
 // launch's work-groups).  The counter is zeroed by the table-padding kernel
 // that precedes every forward launch.  Each item still writes its own partial
 // row, so the result does not depend on which work-group took it.
-template <int QC, int BJ>
-__global__ __launch_bounds__(kWave, forward_waves(QC, BJ, false)) void k_forward_persist(ForwardArgs a) {
+template <int QC, int BJ, bool DIRECT = false>
+__global__ __launch_bounds__(kWave, forward_waves(QC, BJ, DIRECT)) void k_forward_persist(ForwardArgs a) {
+  if (a.fallback && *a.fallback == 0) return;
   const int nchunks = (a.Nq + a.qc - 1) / a.qc;
 #pragma unroll 1
   for (;;) {
@@ -333,13 +336,13 @@ __global__ __launch_bounds__(kWave, forward_waves(QC, BJ, false)) void k_forward
     // q steps)
     int lane = threadIdx.x;
     asm volatile("" : "+v"(lane));
-    forward_strip<QC, BJ, false, false>(a, static_cast<int64_t>(w / nchunks), static_cast<int>(w % nchunks), lane);
+    forward_strip<QC, BJ, DIRECT, false>(a, static_cast<int64_t>(w / nchunks), static_cast<int>(w % nchunks), lane);
   }
 }
 
-// Work-groups of k_forward_persist<QC, BJ> resident on the current GPU (the
-// occupancy query, cached per template and device).
-template <int QC, int BJ>
+// Work-groups of k_forward_persist resident on the current GPU (the occupancy
+// query, cached per template and device).
+template <int QC, int BJ, bool DIRECT>
 int64_t persist_slots() {
   constexpr int kMaxDev = 64;
   static std::atomic<int64_t> cache[kMaxDev];  // 0: not queried yet
@@ -352,7 +355,7 @@ int64_t persist_slots() {
   int per_cu = 0;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_forward_persist<QC, BJ>, kWave, 0) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_forward_persist<QC, BJ, DIRECT>, kWave, 0) != hipSuccess ||
       per_cu <= 0)
     return 0;
   const int64_t slots = static_cast<int64_t>(per_cu) * prop.multiProcessorCount;
@@ -360,23 +363,23 @@ int64_t persist_slots() {
   return slots;
 }
 
-template <int QC>
+template <int QC, bool DIRECT = false>
 hipError_t launch_forward_persist_qc(const ForwardArgs& a, hipStream_t st) {
   int64_t slots = 0;
   switch (a.geo.bj) {
-    case 64: slots = persist_slots<QC, 64>(); break;
-    case 128: slots = persist_slots<QC, 128>(); break;
-    case 256: slots = persist_slots<QC, 256>(); break;
-    case 512: slots = persist_slots<QC, 512>(); break;
+    case 64: slots = persist_slots<QC, 64, DIRECT>(); break;
+    case 128: slots = persist_slots<QC, 128, DIRECT>(); break;
+    case 256: slots = persist_slots<QC, 256, DIRECT>(); break;
+    case 512: slots = persist_slots<QC, 512, DIRECT>(); break;
     default: return hipErrorInvalidValue;
   }
   if (slots <= 0) return hipErrorInvalidValue;
   const dim3 grid(static_cast<uint32_t>(a.n_work < slots ? a.n_work : slots));
   switch (a.geo.bj) {
-    case 64: hipLaunchKernelGGL((k_forward_persist<QC, 64>), grid, dim3(kWave), 0, st, a); break;
-    case 128: hipLaunchKernelGGL((k_forward_persist<QC, 128>), grid, dim3(kWave), 0, st, a); break;
-    case 256: hipLaunchKernelGGL((k_forward_persist<QC, 256>), grid, dim3(kWave), 0, st, a); break;
-    case 512: hipLaunchKernelGGL((k_forward_persist<QC, 512>), grid, dim3(kWave), 0, st, a); break;
+    case 64: hipLaunchKernelGGL((k_forward_persist<QC, 64, DIRECT>), grid, dim3(kWave), 0, st, a); break;
+    case 128: hipLaunchKernelGGL((k_forward_persist<QC, 128, DIRECT>), grid, dim3(kWave), 0, st, a); break;
+    case 256: hipLaunchKernelGGL((k_forward_persist<QC, 256, DIRECT>), grid, dim3(kWave), 0, st, a); break;
+    case 512: hipLaunchKernelGGL((k_forward_persist<QC, 512, DIRECT>), grid, dim3(kWave), 0, st, a); break;
   }
   return hipGetLastError();
 }

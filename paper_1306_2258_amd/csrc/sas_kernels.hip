@@ -19,10 +19,13 @@
 //            diagonal sum_a n_a f_a^2, the 2/q factor and the exact q = 0 value.
 #include <hip/hip_runtime.h>
 
+#include "sas_bins.hpp"
+#include "sas_bins_device.hpp"
 #include "sas_device.hpp"
 #include "sas_forward.hpp"
 #include "sas_forward_kernel.hpp"
 #include "sas_kernels.hpp"
+#include "sas_reduce.hpp"
 #include "sas_schedule.hpp"
 
 namespace sas {
@@ -32,10 +35,59 @@ int64_t slices_of(int64_t n_strips) { return ceil_div(n_strips, kSliceTiles); }
 // ---------------------------------------------------------------------------
 // Pack: stable counting sort by type, per structure, in blocks of kPackBlock.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kPackBlock) void k_pack_count(const int32_t* __restrict__ types, DescView sd, int32_t T,
-                                                           int32_t* __restrict__ bcount) {
+// With the binned form, also each block's bounding box (a coordinate that is
+// not finite makes it infinite) and the padded table.
+__device__ void block_bounds(const float* __restrict__ coords, bool live, int64_t src, float* __restrict__ out) {
+  __shared__ float ext[kPackBlock / kWave][6];
+  float e[6];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    float x = live ? coords[3 * src + c] : 0.f;
+    const bool bad = live && !isfinite(x);
+    e[c] = !live ? INFINITY : (bad ? -INFINITY : x);
+    e[3 + c] = !live ? -INFINITY : (bad ? INFINITY : x);
+  }
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      e[c] = fminf(e[c], __shfl_xor(e[c], off, kWave));
+      e[3 + c] = fmaxf(e[3 + c], __shfl_xor(e[3 + c], off, kWave));
+    }
+  }
+  if (threadIdx.x % kWave == 0)
+    for (int c = 0; c < 6; ++c) ext[threadIdx.x / kWave][c] = e[c];
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    const int c = threadIdx.x;
+    float v = ext[0][c];
+    for (int k = 1; k < kPackBlock / kWave; ++k) v = c < 3 ? fminf(v, ext[k][c]) : fmaxf(v, ext[k][c]);
+    out[c] = v;
+  }
+}
+
+__device__ void pad_table(const float* __restrict__ table, int32_t T, int32_t Nq, int32_t ldt,
+                          float* __restrict__ tabp, unsigned long long* __restrict__ counter, int64_t first,
+                          int64_t stride) {
+  if (first == 0 && counter) *counter = 0ull;
+  for (int64_t k = first; k < static_cast<int64_t>(T) * ldt; k += stride) {
+    const int64_t t = k / ldt;
+    const int32_t m = static_cast<int32_t>(k - t * ldt);
+    tabp[k] = m < Nq ? table[t * Nq + m] : 0.f;
+  }
+}
+
+__global__ __launch_bounds__(kPackBlock) void k_pack_count(const float* __restrict__ coords,
+                                                           const int32_t* __restrict__ types, DescView sd, int32_t T,
+                                                           int32_t* __restrict__ bcount,
+                                                           const float* __restrict__ table, int32_t Nq, int32_t ldt,
+                                                           float* __restrict__ tabp,
+                                                           unsigned long long* __restrict__ counter,
+                                                           float* __restrict__ bbox) {
   extern __shared__ int32_t cnt[];
   const int64_t b = blockIdx.x;
+  if (tabp)
+    pad_table(table, T, Nq, ldt, tabp, counter, b * kPackBlock + threadIdx.x,
+              static_cast<int64_t>(gridDim.x) * kPackBlock);
   const int s = find_struct_by_pack(sd, b);
   const StructDesc d = sd.get(s);
   for (int t = threadIdx.x; t < T; t += blockDim.x) cnt[t] = 0;
@@ -44,6 +96,7 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_count(const int32_t* __rest
   if (a < d.n) atomicAdd(&cnt[clamp_type(types[d.atom_off + a], T)], 1);
   __syncthreads();
   for (int t = threadIdx.x; t < T; t += blockDim.x) bcount[b * T + t] = cnt[t];
+  if (bbox) block_bounds(coords, a < d.n, d.atom_off + a, bbox + b * 6);
 }
 
 // One work-group per structure.  Per type, an exclusive scan of its per-block
@@ -51,8 +104,11 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_count(const int32_t* __rest
 // time); then the type segments' absolute starts toff[s][0..T] in type
 // order; then every block's destination base of every type is that start
 // plus its exclusive count.
+//
+// With the binned form, also the structure's bin count from its bounding box,
+// and for a single structure the planning (a batch has its own kernel for it).
 __global__ __launch_bounds__(256) void k_pack_scan(DescView sd, int32_t T, int32_t* __restrict__ bcount,
-                                                   int32_t* __restrict__ toff) {
+                                                   int32_t* __restrict__ toff, BinArgs bins) {
   extern __shared__ int32_t tot[];
   const int s = blockIdx.x;
   const StructDesc d = sd.get(s);
@@ -89,15 +145,52 @@ __global__ __launch_bounds__(256) void k_pack_scan(DescView sd, int32_t T, int32
   __syncthreads();
   int32_t* base = bcount + static_cast<int64_t>(d.pack_off) * T;
   for (int64_t k = threadIdx.x; k < nb * T; k += blockDim.x) base[k] += tot[k % T];
+  if (!bins.on) return;
+  __shared__ float ext[4][6];
+  float e[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  for (int64_t k = threadIdx.x; k < nb; k += blockDim.x) {
+    const float* p = bins.bbox + (d.pack_off + k) * 6;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      e[c] = fminf(e[c], p[c]);
+      e[3 + c] = fmaxf(e[3 + c], p[3 + c]);
+    }
+  }
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      e[c] = fminf(e[c], __shfl_xor(e[c], off, kWave));
+      e[3 + c] = fmaxf(e[3 + c], __shfl_xor(e[3 + c], off, kWave));
+    }
+  }
+  if (lane == 0)
+    for (int c = 0; c < 6; ++c) ext[w][c] = e[c];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double sq = 0.0;
+    for (int c = 0; c < 3; ++c) {
+      const float lo = fminf(fminf(ext[0][c], ext[1][c]), fminf(ext[2][c], ext[3][c]));
+      const float hi = fmaxf(fmaxf(ext[0][c + 3], ext[1][c + 3]), fmaxf(ext[2][c + 3], ext[3][c + 3]));
+      const double x = d.n > 0 ? static_cast<double>(hi) - static_cast<double>(lo) : 0.0;
+      sq = fma(x, x, sq);
+    }
+    bins.nbins[s] = bin_count(bins, sqrt(sq), d.n);
+  }
+  __syncthreads();
+  if (bins.S == 1) bins_plan(bins, sd, toff);
 }
 
 __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __restrict__ coords,
                                                              const int32_t* __restrict__ types, DescView sd,
                                                              int32_t T, const int32_t* __restrict__ bcount,
                                                              double4* __restrict__ xyz, int32_t* __restrict__ tsort,
-                                                             int32_t* __restrict__ perm) {
+                                                             int32_t* __restrict__ perm, BinArgs bins) {
   __shared__ int32_t ty[kPackBlock];
   const int64_t b = blockIdx.x;
+  if (bins.on) {  // clear the sums of the bins in use
+    const int64_t words = bins.meta->pool_used * kBinMoments, stride = static_cast<int64_t>(gridDim.x) * kPackBlock;
+    for (int64_t k = b * kPackBlock + threadIdx.x; k < words; k += stride) bins.pool[k] = 0;
+  }
   const int s = find_struct_by_pack(sd, b);
   const StructDesc d = sd.get(s);
   const int64_t first = (b - d.pack_off) * kPackBlock;
@@ -111,7 +204,15 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __rest
   for (int p = 0; p < static_cast<int>(threadIdx.x); ++p) rank += (ty[p] == t);
   const int64_t dest = static_cast<int64_t>(bcount[b * T + t]) + rank;
   const int64_t src = d.atom_off + a;
-  xyz[dest] = make_double4(coords[3 * src], coords[3 * src + 1], coords[3 * src + 2], 0.0);
+  const double x = coords[3 * src], y = coords[3 * src + 1], z = coords[3 * src + 2];
+  xyz[dest] = make_double4(x, y, z, 0.0);
+  if (bins.on) {
+    const int32_t* o = bins.toff + static_cast<int64_t>(s) * (T + 1) + t;
+    double* to = bins.xs + 3 * (o[0] + bin_spread(static_cast<int32_t>(dest - o[0]), o[1] - o[0]));
+    to[0] = x * bins.invh;
+    to[1] = y * bins.invh;
+    to[2] = z * bins.invh;
+  }
   tsort[dest] = t;
   perm[dest] = static_cast<int32_t>(src);
 }
@@ -120,12 +221,8 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __rest
 __global__ __launch_bounds__(256) void k_pad_table(const float* __restrict__ table, int32_t T, int32_t Nq,
                                                    int32_t ldt, float* __restrict__ tabp,
                                                    unsigned long long* __restrict__ counter) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (k == 0 && counter) *counter = 0ull;
-  if (k >= static_cast<int64_t>(T) * ldt) return;
-  const int64_t t = k / ldt;
-  const int32_t m = static_cast<int32_t>(k - t * ldt);
-  tabp[k] = m < Nq ? table[t * Nq + m] : 0.f;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  pad_table(table, T, Nq, ldt, tabp, counter, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride);
 }
 
 // Input check of the debug mode: flags[0] and flags[1] count atoms with a
@@ -167,17 +264,31 @@ hipError_t launch_pad_table(const float* table, int32_t T, int32_t Nq, int32_t l
 
 hipError_t launch_pack(const float* coords, const int32_t* types, const DescView& sd, int32_t S,
                        int64_t n_pack_blocks, int32_t T, int32_t* bcount, int32_t* toff, double4* xyz,
-                       int32_t* tsort, int32_t* perm, hipStream_t st) {
+                       int32_t* tsort, int32_t* perm, const float* table, int32_t Nq, int32_t ldt, float* tabp,
+                       unsigned long long* counter, const BinArgs* bins, hipStream_t st) {
+  const BinArgs b = bins ? *bins : BinArgs{};
+  // the counting kernel pads the table on the side, unless it has too few
+  // threads for its size
+  const bool pad = n_pack_blocks > 0 && static_cast<int64_t>(T) * ldt <= 16 * kPackBlock * n_pack_blocks;
+  if (!pad) {
+    const hipError_t e = launch_pad_table(table, T, Nq, ldt, tabp, st, counter);
+    if (e != hipSuccess) return e;
+  }
   if (n_pack_blocks > 0) {
     hipLaunchKernelGGL(k_pack_count, dim3(static_cast<uint32_t>(n_pack_blocks)), dim3(kPackBlock),
-                       sizeof(int32_t) * T, st, types, sd, T, bcount);
+                       sizeof(int32_t) * T, st, coords, types, sd, T, bcount, table, Nq, ldt, pad ? tabp : nullptr,
+                       counter, b.bbox);
   }
   if (S > 0) {
-    hipLaunchKernelGGL(k_pack_scan, dim3(S), dim3(256), sizeof(int32_t) * T, st, sd, T, bcount, toff);
+    hipLaunchKernelGGL(k_pack_scan, dim3(S), dim3(256), sizeof(int32_t) * T, st, sd, T, bcount, toff, b);
+    if (b.on && S > 1) {
+      const hipError_t e = launch_bins_plan(b, sd, toff, st);
+      if (e != hipSuccess) return e;
+    }
   }
   if (n_pack_blocks > 0) {
     hipLaunchKernelGGL(k_pack_scatter, dim3(static_cast<uint32_t>(n_pack_blocks)), dim3(kPackBlock), 0, st, coords,
-                       types, sd, T, bcount, xyz, tsort, perm);
+                       types, sd, T, bcount, xyz, tsort, perm, b);
   }
   return hipGetLastError();
 }
@@ -199,8 +310,9 @@ hipError_t launch_forward(const ForwardArgs& a, int64_t n_strips_total, int32_t 
   const int nchunks = static_cast<int>(ceil_div(a.Nq, a.qc));
   const dim3 grid(static_cast<uint32_t>(n_strips_total), nchunks);
   if (a.counter) {
-    // persistent launch (recurrence form only)
-    if (a.qdev || a.n_work != n_strips_total * nchunks) return hipErrorInvalidValue;
+    // persistent launch (the direct form takes it only behind the binned form)
+    if (a.n_work != n_strips_total * nchunks) return hipErrorInvalidValue;
+    if (a.qdev) return qc_template == 32 ? launch_forward_persist_qc<32, true>(a, st) : hipErrorInvalidValue;
     switch (qc_template) {
       case 16: return launch_forward_persist_qc<16>(a, st);
       case 32: return launch_forward_persist_qc<32>(a, st);
@@ -242,27 +354,10 @@ hipError_t launch_forward(const ForwardArgs& a, int64_t n_strips_total, int32_t 
 // results are deterministic.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_reduce_slices(DescView sd, const double* __restrict__ partial, int32_t Nq,
-                                                       double* __restrict__ slice_sums) {
-  __shared__ double part[4][kWave];
-  const int64_t sl = blockIdx.x;
-  const int s = find_struct_by_slice(sd, sl);
-  const StructDesc d = sd.get(s);
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-  const int64_t first = d.strip_off + (sl - d.slice_off) * kSliceTiles;
-  const int64_t last = min(first + kSliceTiles, d.strip_off + d.n_strips);
-  constexpr int kQuarter = kSliceTiles / 4;
-  const int64_t a = first + w * kQuarter, b = min(last, a + kQuarter);
-  const int groups = static_cast<int>(ceil_div(Nq, kWave));
-  for (int g = blockIdx.y; g < groups; g += gridDim.y) {  // (grid.y is capped at 65535)
-    const int m = g * kWave + lane;
-    double acc = 0.0;
-    if (m < Nq)
-      for (int64_t t = a; t < b; ++t) acc += partial[t * Nq + m];
-    __syncthreads();
-    part[w][lane] = acc;
-    __syncthreads();
-    if (w == 0 && m < Nq) slice_sums[sl * Nq + m] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-  }
+                                                       double* __restrict__ slice_sums,
+                                                       const int32_t* __restrict__ fallback) {
+  if (fallback && *fallback == 0) return;
+  reduce_slice(sd, blockIdx.x, partial, Nq, slice_sums);
 }
 
 __global__ __launch_bounds__(256) void k_reduce_final(DescView sd, const double* __restrict__ slice_sums,
@@ -270,12 +365,14 @@ __global__ __launch_bounds__(256) void k_reduce_final(DescView sd, const double*
                                                       const double* __restrict__ asum,
                                                       const float* __restrict__ table, int32_t T, int32_t Nq,
                                                       double q0, double dq, const double* __restrict__ qdev,
-                                                      double* __restrict__ I_out) {
+                                                      BinArgs b, double* __restrict__ I_out) {
   __shared__ double part[4][kWave];
   const int s = blockIdx.x;
   const StructDesc d = sd.get(s);
   const int32_t* o = toff ? toff + static_cast<int64_t>(s) * (T + 1) : nullptr;
   const int64_t nb = ceil_div(d.n, kPackBlock);
+  // a binned structure's pair sums are complete (no 2/q factor)
+  const bool binned = b.on && b.route[s];
   const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   const int groups = static_cast<int>(ceil_div(Nq, kWave));
   for (int g = blockIdx.y; g < groups; g += gridDim.y) {  // (grid.y is capped at 65535)
@@ -284,8 +381,18 @@ __global__ __launch_bounds__(256) void k_reduce_final(DescView sd, const double*
     const double qm = vm ? (qdev ? qdev[m] : q0 + m * dq) : 1.0;
     // the strip pair sums: wave w takes slices w, w + 4, ... in order
     double pairs = 0.0;
-    if (vm && qm != 0.0)
-      for (int64_t k = w; k < d.n_slices; k += 4) pairs += slice_sums[(d.slice_off + k) * Nq + m];
+    if (vm && qm != 0.0) {
+      if (binned) {
+        // (in order, by the first wave: one work-group that adds its own rows
+        // gives the same sum)
+        const int rows = w == 0 ? bin_rows(b, b.nbins[s]) : 0;
+        const double* p = b.part + static_cast<int64_t>(s) * b.rows * Nq + m;
+#pragma unroll 16
+        for (int k = 0; k < rows; ++k) pairs += p[static_cast<int64_t>(k) * Nq];
+      } else {
+        for (int64_t k = w; k < d.n_slices; k += 4) pairs += slice_sums[(d.slice_off + k) * Nq + m];
+      }
+    }
     __syncthreads();
     part[w][lane] = pairs;
     __syncthreads();
@@ -311,7 +418,7 @@ __global__ __launch_bounds__(256) void k_reduce_final(DescView sd, const double*
             diag += static_cast<double>(o[t + 1] - o[t]) * f * f;
           }
         }
-        val = diag + (2.0 / qm) * psum;
+        val = binned ? diag + psum : diag + (2.0 / qm) * psum;
       }
       I_out[static_cast<int64_t>(d.orig) * Nq + m] = val;
     }
@@ -319,10 +426,21 @@ __global__ __launch_bounds__(256) void k_reduce_final(DescView sd, const double*
 }
 
 hipError_t launch_reduce_slices(const DescView& sd, int64_t n_slices_total, const double* partial, int32_t row,
-                                double* slice_sums, hipStream_t st) {
+                                double* slice_sums, const int32_t* fallback, hipStream_t st) {
   if (n_slices_total > 0) {
     const dim3 grid(static_cast<uint32_t>(n_slices_total), static_cast<uint32_t>(std::min<int64_t>(ceil_div(row, kWave), 65535)));
-    hipLaunchKernelGGL(k_reduce_slices, grid, dim3(256), 0, st, sd, partial, row, slice_sums);
+    hipLaunchKernelGGL(k_reduce_slices, grid, dim3(256), 0, st, sd, partial, row, slice_sums, fallback);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_final(const DescView& sd, int32_t S, const double* slice_sums, const int32_t* toff,
+                               const double* asum, const float* table, int32_t T, int32_t Nq, double q0, double dq,
+                               const double* qdev, const BinArgs* bins, double* I_out, hipStream_t st) {
+  const uint32_t qgroups = static_cast<uint32_t>(std::min<int64_t>(ceil_div(Nq, kWave), 65535));
+  if (S > 0) {
+    hipLaunchKernelGGL(k_reduce_final, dim3(S, qgroups), dim3(256), 0, st, sd, slice_sums, toff, asum, table, T, Nq,
+                       q0, dq, qdev, bins ? *bins : BinArgs{}, I_out);
   }
   return hipGetLastError();
 }
@@ -333,13 +451,9 @@ hipError_t launch_reduce(const DescView& sd, int32_t S, int64_t n_slices_total, 
   const uint32_t qgroups = static_cast<uint32_t>(std::min<int64_t>(ceil_div(Nq, kWave), 65535));
   if (n_slices_total > 0) {
     hipLaunchKernelGGL(k_reduce_slices, dim3(static_cast<uint32_t>(n_slices_total), qgroups), dim3(256), 0, st, sd,
-                       partial, Nq, slice_sums);
+                       partial, Nq, slice_sums, nullptr);
   }
-  if (S > 0) {
-    hipLaunchKernelGGL(k_reduce_final, dim3(S, qgroups), dim3(256), 0, st, sd, slice_sums, toff, asum, table, T, Nq,
-                       q0, dq, qdev, I_out);
-  }
-  return hipGetLastError();
+  return launch_reduce_final(sd, S, slice_sums, toff, asum, table, T, Nq, q0, dq, qdev, nullptr, I_out, st);
 }
 
 }  // namespace sas

@@ -67,6 +67,9 @@ struct ForwardArgs {
   int32_t rows_ld;      // q stride of rows (>= Nq)
   unsigned long long* counter;  // persistent launch: next (strip, chunk) item; null for a grid launch
   int64_t n_work;               // persistent launch: strips x chunks
+  // with the binned form: the structures left to this kernel (null: all)
+  const int32_t* route;     // [S] 0: left to this kernel
+  const int32_t* fallback;  // their number
 };
 
 constexpr int kAdjQ = 512;  // q values per adjoint chunk (weights staged in LDS)
@@ -88,16 +91,20 @@ struct AdjArgs {
   int64_t n_strips;
   double q0, dq;
   const double* qdev;   // non-null: arbitrary grid [Nq] on the device (direct variant)
+  const int32_t* route; // non-null: [0] = 1 when the binned form does the work
 };
+
+struct BinArgs;  // the binned form (sas_bins.hpp)
 
 // Host-side helpers implemented in sas_kernels.hip / sas_adjoint.hip.
 int64_t slices_of(int64_t n_strips);
 
 hipError_t launch_pack(const float* coords, const int32_t* types, const DescView& sd, int32_t S,
                        int64_t n_pack_blocks, int32_t T, int32_t* bcount, int32_t* toff, double4* xyz,
-                       int32_t* tsort, int32_t* perm, hipStream_t st);
-// Also zeroes *counter (when non-null), the work counter of a persistent
-// forward launch that follows on the same stream.
+                       int32_t* tsort, int32_t* perm, const float* table, int32_t Nq, int32_t ldt, float* tabp,
+                       unsigned long long* counter, const BinArgs* bins, hipStream_t st);
+// Both also zero *counter (when non-null), the work counter of a persistent
+// forward launch that follows on the same stream; the pack pads the table too.
 hipError_t launch_pad_table(const float* table, int32_t T, int32_t Nq, int32_t ldt, float* tabp, hipStream_t st,
                             unsigned long long* counter = nullptr);
 hipError_t launch_validate(const float* coords, const int32_t* types, int64_t n, int32_t T, unsigned long long* flags,
@@ -110,16 +117,23 @@ hipError_t launch_reduce(const DescView& sd, int32_t S, int64_t n_slices_total, 
                          double* slice_sums, const int32_t* toff, const double* asum, const float* table, int32_t T,
                          int32_t Nq, double q0, double dq, const double* qdev, double* I_out, hipStream_t st);
 
-// Sum rows of `row` values over each slice of kSliceTiles strips, in order.
+// The second level alone; with `bins`, a binned structure's pair sums come from
+// its partial profiles there.
+hipError_t launch_reduce_final(const DescView& sd, int32_t S, const double* slice_sums, const int32_t* toff,
+                               const double* asum, const float* table, int32_t T, int32_t Nq, double q0, double dq,
+                               const double* qdev, const BinArgs* bins, double* I_out, hipStream_t st);
+
+// Sum rows of `row` values over each slice of kSliceTiles strips, in order
+// (nothing when *fallback is given and 0).
 hipError_t launch_reduce_slices(const DescView& sd, int64_t n_slices_total, const double* partial, int32_t row,
-                                double* slice_sums, hipStream_t st);
+                                double* slice_sums, const int32_t* fallback, hipStream_t st);
 
 // Table gradient (sas_tablegrad.hip): the forward pass that also writes the
 // per-type sums, and the final step that forms w_m dI/df_t(q_m).
 hipError_t launch_forward_tg(const ForwardArgs& a, int64_t n_strips_total, int32_t qc_template, hipStream_t st);
 hipError_t launch_table_grad_final(int64_t n_slices, const double* gslices, const int32_t* toff,
                                    const float* table, int32_t T, int32_t Nq, double q0, double dq, const double* qdev,
-                                   const double* w, double* grad_table, hipStream_t st);
+                                   const double* w, const BinArgs* bins, double* grad_table, hipStream_t st);
 
 // Orientation-averaged profile (sas_orient.hip).
 constexpr int kOrientQ = 16;  // q values per orientation chunk (one quadrature per chunk)

@@ -29,6 +29,8 @@
 
 #include <algorithm>
 
+#include "sas_bins.hpp"
+#include "sas_bins_device.hpp"
 #include "sas_forward_kernel.hpp"
 #include "sas_kernels.hpp"
 #include "sas_schedule.hpp"
@@ -65,7 +67,7 @@ __global__ __launch_bounds__(256) void k_table_grad_final(int64_t n_slices,
                                                           const int32_t* __restrict__ toff,
                                                           const float* __restrict__ table, int32_t T, int32_t Nq,
                                                           double q0, double dq, const double* __restrict__ qdev,
-                                                          const double* __restrict__ w,
+                                                          const double* __restrict__ w, BinArgs bins,
                                                           double* __restrict__ grad_table) {
   const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (k >= static_cast<int64_t>(T) * Nq) return;
@@ -81,6 +83,20 @@ __global__ __launch_bounds__(256) void k_table_grad_final(int64_t n_slices,
     d_f = 2.0 * nt * f1;
   } else {
     double g = 0.0;
+    if (bins.on && bins.route[0]) {
+      // binned: sums of sinc(q r) per type pair, times the other type's factor
+      // (twice its own within one type)
+      const int rows = bin_rows(bins, bins.nbins[0]);
+      for (int b = 0; b < T; ++b) {
+        const int lo = t < b ? t : b, hi = t < b ? b : t;
+        const int64_t tp = static_cast<int64_t>(hi) * (hi + 1) / 2 + lo;
+        double s = 0.0;
+        for (int k2 = 0; k2 < rows; ++k2) s += bins.spart[(k2 * static_cast<int64_t>(bins.TP) + tp) * Nq + m];
+        g = fma((b == t ? 2.0 : 1.0) * static_cast<double>(table[static_cast<int64_t>(b) * Nq + m]), s, g);
+      }
+      grad_table[k] = w[m] * 2.0 * (nt * static_cast<double>(table[k]) + g);
+      return;
+    }
     for (int64_t sl = 0; sl < n_slices; ++sl) g += gslices[(sl * T + t) * static_cast<int64_t>(Nq) + m];
     d_f = 2.0 * nt * static_cast<double>(table[k]) + (2.0 / qm) * g;
   }
@@ -89,10 +105,10 @@ __global__ __launch_bounds__(256) void k_table_grad_final(int64_t n_slices,
 
 hipError_t launch_table_grad_final(int64_t n_slices, const double* gslices, const int32_t* toff,
                                    const float* table, int32_t T, int32_t Nq, double q0, double dq, const double* qdev,
-                                   const double* w, double* grad_table, hipStream_t st) {
+                                   const double* w, const BinArgs* bins, double* grad_table, hipStream_t st) {
   const int64_t total = static_cast<int64_t>(T) * Nq;
   hipLaunchKernelGGL(k_table_grad_final, dim3(static_cast<uint32_t>(ceil_div(total, 256))), dim3(256), 0, st,
-                     n_slices, gslices, toff, table, T, Nq, q0, dq, qdev, w, grad_table);
+                     n_slices, gslices, toff, table, T, Nq, q0, dq, qdev, w, bins ? *bins : BinArgs{}, grad_table);
   return hipGetLastError();
 }
 
