@@ -151,6 +151,7 @@ __global__ __launch_bounds__(kWave) void k_adjoint(AdjArgs a) {
   float* ul = reinterpret_cast<float*>(ul4);
   float* vl = reinterpret_cast<float*>(vl4);
 
+  if (a.binned && *a.binned) return;
   const int lane = threadIdx.x;
   const int64_t t = blockIdx.x;
   const StructDesc d = a.sd.get(0);
@@ -642,6 +643,7 @@ __global__ __launch_bounds__(kGradParts * kGradAtoms) void k_grad_reduce(AdjArgs
                                                                         const int32_t* __restrict__ perm,
                                                                         double* __restrict__ grad_out) {
   __shared__ double red[kGradParts][kGradAtoms][3];
+  if (a.binned && *a.binned) return;
   const StructDesc d = a.sd.get(0);
   const int part = threadIdx.x / kGradAtoms, al = threadIdx.x % kGradAtoms;
   const int64_t at = static_cast<int64_t>(blockIdx.x) * kGradAtoms + al;

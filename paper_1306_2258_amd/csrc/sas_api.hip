@@ -162,6 +162,7 @@ struct Schedule {
   int32_t tg_types = 0;   // > 0: the forward also writes per-type table-gradient rows
   bool bins = false;      // the binned form, with the forward kernel for what it leaves
   BinArgs ba{};           // its sizes (no pointers)
+  int64_t bin_units = 0;  // binned gradient: at least its work units
   int32_t qc = 0, qc_template = 0;
   int32_t nchunks = 0, ldt = 0;  // q chunks; row stride of the padded table
   // adjoint (gradient) schedule, single structure only
@@ -183,8 +184,8 @@ struct Layout {
   size_t gpart = 0, gslices = 0;  // table gradient: [strips][T][Nq], [slices][T][Nq]
   size_t counter = 0;             // persistent launch: the work counter
   // binned form
-  size_t bxs = 0, bbox = 0, bnbins = 0, broute = 0, bpooloff = 0, bmeta = 0, bentries = 0, bpool = 0, bpart = 0,
-         bspart = 0;
+  size_t bxs = 0, bcentre = 0, bbox = 0, bnbins = 0, broute = 0, bpooloff = 0, bmeta = 0, bentries = 0, bpool = 0, bpart = 0,
+         bspart = 0, bgents = 0, border = 0, bfield = 0, bgpart = 0;
   // host-written block, uploaded in one copy: structure descriptors (S > 1)
   // followed by the q grid (direct form)
   size_t upload = 0, upload_bytes = 0, desc = 0, qdev = 0;
@@ -388,7 +389,7 @@ void add_bins(Schedule* sc, const sas_ctx* ctx, const std::vector<int64_t>& size
   b.alt_steps = direct_steps(Nq, !sc->direct);
   // items of 64 by 64 atoms, or shorter ones when those would leave CUs idle
   const double tiles = pairs / (64.0 * 64.0);
-  b.sub = tiles >= 16384.0 ? 1 : (tiles >= 8192.0 ? 2 : (tiles >= 2048.0 ? 4 : 8));
+  b.sub = tiles >= 16384.0 ? 1 : (tiles >= 8192.0 ? 2 : 4);
   // one work-group per CU, each with at least eight items: a smaller share costs
   // more in emptying the bins than it saves
   b.pair_wgs = static_cast<int32_t>(
@@ -413,6 +414,16 @@ void add_bins(Schedule* sc, const sas_ctx* ctx, const std::vector<int64_t>& size
   b.wgs = static_cast<int32_t>(std::min<int64_t>(sas::kBinGroups, std::max<int64_t>(1, 512 / (S * qgroups))));
   b.rows = b.wgs == 1 && sc->tg_types == 0 ? 1 : sas::kBinGroups;
   sc->bins = true;
+}
+
+// Adds the binned coordinate gradient to a binned schedule of one structure:
+// units of 64 atoms by `span`, about four per CU or more.
+void add_bins_grad(Schedule* sc, int64_t n, int32_t T) {
+  if (!sc->bins || n < 2) return;
+  const int64_t want = n * n / 65536;
+  const int64_t span = std::min<int64_t>(8192, std::max<int64_t>(64, (want + 63) / 64 * 64));
+  sc->ba.span = static_cast<int32_t>(span);
+  sc->bin_units = (n / sas::kWave + T) * (n / span + T);
 }
 
 // make_schedule with the automatic shape, and the binned form where it serves.
@@ -545,12 +556,19 @@ Layout make_layout(const Schedule& sc, int32_t T, int32_t Nq) {
   const size_t rows = sizeof(double) * sc.n_strips * Nq;
   if (sc.bins) {
     const BinArgs& b = sc.ba;
-    L.bxs = take(sizeof(double) * 3 * (sc.n_total + sas::kBinPad));
+    L.bxs = take(sizeof(double) * 4 * (sc.n_total + sas::kBinPad));
+    L.bcentre = take(sizeof(double) * 3 * b.S);
     L.bbox = take(sizeof(float) * 6 * sc.n_pack);
     L.bnbins = take(sizeof(int32_t) * b.S);
     L.broute = take(sizeof(int32_t) * b.S);
     L.bpooloff = take(sizeof(int64_t) * b.S);
     L.bmeta = take(sizeof(sas::BinMeta));
+    if (b.span > 0) {
+      L.bgents = take(sizeof(sas::GradEntry) * (static_cast<size_t>(b.T) * b.T + 1));
+      L.border = take(sizeof(int32_t) * sc.n_total);
+      L.bfield = take(sizeof(float) * sas::kBinMoments * static_cast<size_t>(b.TP) * std::min(b.max_bins, sas::kBinCap));
+      L.bgpart = take(sizeof(double) * 4 * sas::kWave * static_cast<size_t>(sc.bin_units));
+    }
     L.bentries = take(sizeof(sas::BinEntry) * (static_cast<size_t>(b.S) * b.TP + 1));
     const size_t pool = align_up(sizeof(unsigned long long) * sas::kBinMoments * static_cast<size_t>(b.pool_cap));
     const size_t part = align_up(sizeof(double) * static_cast<size_t>(b.S) * b.rows * Nq);
@@ -609,6 +627,8 @@ BinArgs bins_of(const Schedule& sc, void* ws, const Layout& L) {
   BinArgs b = sc.ba;
   char* w = static_cast<char*>(ws);
   b.xs = reinterpret_cast<double*>(w + L.bxs);
+  b.ld = sc.n_total + sas::kBinPad;
+  b.centre = reinterpret_cast<double*>(w + L.bcentre);
   b.toff = reinterpret_cast<const int32_t*>(w + L.toff);
   b.bbox = reinterpret_cast<float*>(w + L.bbox);
   b.nbins = reinterpret_cast<int32_t*>(w + L.bnbins);
@@ -618,6 +638,10 @@ BinArgs bins_of(const Schedule& sc, void* ws, const Layout& L) {
   b.entries = reinterpret_cast<sas::BinEntry*>(w + L.bentries);
   b.pool = reinterpret_cast<unsigned long long*>(w + L.bpool);
   b.part = reinterpret_cast<double*>(w + L.bpart);
+  b.gents = reinterpret_cast<sas::GradEntry*>(w + L.bgents);
+  b.order = reinterpret_cast<int32_t*>(w + L.border);
+  b.field = reinterpret_cast<float*>(w + L.bfield);
+  b.gpart = reinterpret_cast<double*>(w + L.bgpart);
   b.spart = sc.tg_types > 0 ? reinterpret_cast<double*>(w + L.bspart) : nullptr;
   return b;
 }
@@ -1154,6 +1178,7 @@ size_t sas_debye_workspace_size(const sas_ctx* ctx, int64_t n, int32_t t, int32_
         add_adjoint_pa(&sc, n, nq);
       else
         add_adjoint(&sc, n, nq);
+      add_bins_grad(&sc, n, t);
       need = std::max(need, make_layout(sc, t, nq).total);
     }
     return need;
@@ -1589,6 +1614,7 @@ sas_status sas_debye_grad(sas_ctx* ctx, const float* coords, const int32_t* type
     add_adjoint_pa(&sc, n, nq);
   else
     add_adjoint(&sc, n, nq);
+  add_bins_grad(&sc, n, t);
   const Layout L = make_layout(sc, t, nq);
   if (!workspace) return fail(SAS_ERR_INVALID_ARG, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign) return fail(SAS_ERR_INVALID_ARG, "workspace not 256-byte aligned");
@@ -1607,6 +1633,9 @@ sas_status sas_debye_grad(sas_ctx* ctx, const float* coords, const int32_t* type
     if (st != SAS_OK) return st;
   } else {
     auto* tabp = reinterpret_cast<float*>(w + L.tabp);
+    // (the plan of the bins is wanted, their sums are not)
+    BinArgs bins = sc.bins ? bins_of(sc, workspace, L) : BinArgs{};
+    bins.pool = nullptr;
     if (pa) {
       SAS_HIP(sas::launch_pad_table(table, t, nq, sc.ldt, tabp, hs));
       SAS_HIP(sas::launch_pack_plain(coords, types, n, t, reinterpret_cast<double4*>(w + L.xyz),
@@ -1616,7 +1645,8 @@ sas_status sas_debye_grad(sas_ctx* ctx, const float* coords, const int32_t* type
       SAS_HIP(sas::launch_pack(coords, types, view_of(sc, workspace, L), sc.S, sc.n_pack, t,
                                reinterpret_cast<int32_t*>(w + L.bcount), reinterpret_cast<int32_t*>(w + L.toff),
                                reinterpret_cast<double4*>(w + L.xyz), reinterpret_cast<int32_t*>(w + L.tsort),
-                               reinterpret_cast<int32_t*>(w + L.perm), table, nq, sc.ldt, tabp, nullptr, nullptr, hs));
+                               reinterpret_cast<int32_t*>(w + L.perm), table, nq, sc.ldt, tabp, nullptr,
+                               sc.bins ? &bins : nullptr, hs));
     }
   }
   if (n == 0) return SAS_OK;
@@ -1639,8 +1669,12 @@ sas_status sas_debye_grad(sas_ctx* ctx, const float* coords, const int32_t* type
   a.q0 = q0;
   a.dq = dq;
   a.qdev = sc.direct ? reinterpret_cast<const double*>(w + L.qdev) : nullptr;
+  const BinArgs gb = sc.ba.span > 0 ? bins_of(sc, workspace, L) : BinArgs{};
+  if (sc.ba.span > 0) a.binned = &gb.meta->grad;
   {
     LaunchTimer timer(ctx, hs, true);
+    if (sc.ba.span > 0)
+      SAS_HIP(sas::launch_bins_grad(gb, n, sc.bin_units, table, dL_dI, nq, q0, dq, a.qdev, grad_out, hs));
     if (pa)
       SAS_HIP(sas::launch_adjoint_pa(a, sc.nchunks_adj, sc.qa_template, hs));
     else

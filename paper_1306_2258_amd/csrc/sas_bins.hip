@@ -104,93 +104,103 @@ __device__ __forceinline__ void empty_bins(unsigned long long* h, const BinSeg* 
   }
 }
 
-// One item: the lane's atom against the swept atoms [j0, j1).
-// What bounds it: per pair ten FP64 instructions, two transcendental and about
-// twenty FP32 or integer ones, and three 64-bit LDS atomics, which random
-// bins serve at about six lanes per cycle and CU (nine from 16 copies of
-// each bin): the vector pipes and LDS take about the same time.
-// Each pair's atomics are issued right after its arithmetic: with a batch's
-// twelve together at its end the waves fell into step, LDS and vector pipes in
-// turn idle (rod, 1.25e9 pairs: 2.44 ms).
-// The swept atoms come through the scalar cache, four at a time.  Scalar loads
-// and LDS operations share one wait counter, so a batch's loads are issued as
-// soon as the last one's coordinates are used up, and waited for before the
-// last pair's atomics.
-constexpr int kBinBatch = 4;
+// The squared distances come from the matrix cores: s = |x_j|^2 - 2 x_i x_j +
+// |x_i|^2 is a product of depth four, [x_j, |x_j|^2] by [-2 x_i, 1], plus a
+// constant per i.  v_mfma_f64_4x4x4 makes 64 of them in 16 cycles beside the
+// vector pipes, which would take seven FP64 instructions for each.  The
+// coordinates are centred, so the cancellation leaves s good to about 1e-9 in
+// units of a bin's width squared, at any distance.
+// Lane l holds the pair of atom i0 + l % 16 (16 lane-side atoms per product)
+// and swept atom j + l / 16.
+using SumWord = unsigned long long;
 
 struct PairWords {
-  uint32_t at, f1, f2, f3, f4, f5;
+  uint32_t bin, f1, f2, f3, f4, f5;
 };
 
-// MASKED: pairs outside [0, count), not above lane_min, or outside the window
-// go to the lane's own spare words past the last bin.
-template <bool MASKED>
-__device__ __forceinline__ PairWords pair_words(double s, int k, uint32_t lane_base, uint32_t bin_bytes, int count,
-                                                int lane_min, int win0, uint32_t bins, uint32_t spare) {
-  const float magic = 0x1.8p+23f;
-  PairWords p;
-  const float fb = __builtin_truncf(__builtin_amdgcn_sqrtf(static_cast<float>(s)));
+// u of a pair and its bin (as a float) from the square s.
+__device__ __forceinline__ float pair_coordinate(double s, float* bin) {
+  // (s may come out a little below zero for atoms that coincide)
+  const float fb = __builtin_truncf(__builtin_amdgcn_sqrtf(fabsf(static_cast<float>(s))));
   const float tc = fb + 0.5f;
   const double tcd = static_cast<double>(tc);
   const float d = static_cast<float>(fma(-tcd, tcd, s));
-  const float u = d * __builtin_amdgcn_rcpf(tc);
+  *bin = fb;
+  return d * __builtin_amdgcn_rcpf(tc);
+}
+
+__device__ __forceinline__ PairWords pair_words(double s) {
+  const float magic = 0x1.8p+23f;
+  PairWords p;
+  float fb;
+  const float u = pair_coordinate(s, &fb);
   const float u2 = u * u, u3 = u2 * u, u4 = u2 * u2, u5 = u4 * u;
   p.f1 = __float_as_uint(fmaf(u, static_cast<float>(1 << kBinBits1), magic));
   p.f2 = __float_as_uint(fmaf(u2, static_cast<float>(1 << kBinBits2), magic));
   p.f3 = __float_as_uint(fmaf(u3, static_cast<float>(1 << kBinBits3), magic));
   p.f4 = __float_as_uint(fmaf(u4, static_cast<float>(1 << kBinBits4), magic)) << kBinShift4;
   p.f5 = __float_as_uint(fmaf(u5, static_cast<float>(1 << kBinBits5), magic)) << kBinShift5;
-  if (MASKED) {
-    const uint32_t bin = static_cast<uint32_t>(static_cast<int>(fb) - win0);
-    p.at = bin < bins && k < count && k > lane_min ? __umul24(bin, bin_bytes) + lane_base : spare;
-  } else {
-    p.at = __umul24(static_cast<uint32_t>(fb), bin_bytes) + lane_base;
-  }
+  p.bin = static_cast<uint32_t>(fb);
   return p;
 }
 
-__device__ __forceinline__ void deposit(unsigned char* hb, const PairWords& p) {
-  auto* to = reinterpret_cast<unsigned long long*>(hb + p.at);
+__device__ __forceinline__ void deposit(unsigned char* at, const PairWords& p) {
+  auto* to = reinterpret_cast<SumWord*>(at);
   atomicAdd(to, (1ull << (32 + kBinCountShift)) | p.f1);
-  atomicAdd(to + 1, (static_cast<unsigned long long>(p.f5) << 32) | p.f2);
-  atomicAdd(to + 2, (static_cast<unsigned long long>(p.f4) << 32) | p.f3);
+  atomicAdd(to + 1, (static_cast<SumWord>(p.f5) << 32) | p.f2);
+  atomicAdd(to + 2, (static_cast<SumWord>(p.f4) << 32) | p.f3);
 }
 
+// One item: lane-side atoms [i0, i0 + 64) against swept atoms [j0, j1).
+// What bounds it: per pair about 22 vector instructions (four FP64 or
+// conversions from it, two transcendental) and three 64-bit LDS atomics, each
+// 4 cycles per wave and CU without bank conflicts (16 copies of each bin) and
+// about 12 with bins at random.  Each pair's atomics are issued right after its
+// arithmetic: with a batch's twelve together at its end the waves fell into
+// step, LDS and vector pipes in turn idle.
+// MASKED: pairs past a segment's end, not above the diagonal or outside the
+// window go to the lane's own spare words past the last bin.
+constexpr int kBinTiles = kWave / 16;  // products per swept quad
 template <bool MASKED>
-__device__ __forceinline__ void sweep(const double* __restrict__ xs, unsigned char* hb, const BinSeg& sg, int i, int j0,
-                                      int j1, bool diag, uint32_t lane_base, uint32_t bin_bytes) {
-  using ConstDouble = const __attribute__((address_space(4))) double;
-  ConstDouble* xj = (ConstDouble*)(xs + 3 * (static_cast<int64_t>(sg.b0) + j0));
-  const double* pi = xs + 3 * (static_cast<int64_t>(sg.a0) + i);
-  const double xi = pi[0], yi = pi[1], zi = pi[2];
-  const uint32_t spare = 24u * (kBinCap + threadIdx.x % kWave);
-  double cj[3 * kBinBatch];
+__device__ __forceinline__ void sweep(const double* __restrict__ xs, int64_t ld, unsigned char* hb, const BinSeg& sg,
+                                      int i0, int j0, int j1, bool diag, uint32_t lane_base, uint32_t bin_bytes) {
+  const int lane = threadIdx.x % kWave;
+  const int li = lane % 16, lk = lane / 16;  // atom and component of an operand; pair (i0 + li, j + lk) of a result
+  const double* xk = xs + lk * ld;
+  const double* pj = xk + sg.b0 + j0 + lane % 4;  // (operand of the swept side: the quad repeated in the four blocks)
+  double bi[kBinTiles], ci[kBinTiles];
 #pragma unroll
-  for (int k = 0; k < 3 * kBinBatch; ++k) cj[k] = xj[k];
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  for (int t = 0; t < kBinTiles; ++t) {
+    const int64_t at = sg.a0 + i0 + 16 * t + li;
+    const double x = xk[at];
+    bi[t] = lk == 3 ? 1.0 : -2.0 * x;
+    ci[t] = xs[3 * ld + at];
+  }
+  const uint32_t spare = 24u * (kBinCap + lane);
+  double next = *pj;
 #pragma unroll 1
-  for (int j = j0; j < j1; j += kBinBatch) {
-    double s[kBinBatch];
+  for (int j = j0; j < j1; j += 4) {
+    const double aj = next;
+    pj += 4;
+    next = *pj;  // (rows past the end are other segments' or the array's padding)
+    double s[kBinTiles];
 #pragma unroll
-    for (int k = 0; k < kBinBatch; ++k) {
-      const double dx = xi - cj[3 * k], dy = yi - cj[3 * k + 1], dz = zi - cj[3 * k + 2];
-      s[k] = fma(dz, dz, fma(dy, dy, dx * dx));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // (rows past the end are other segments' or the array's padding)
-    xj += 3 * kBinBatch;
+    for (int t = 0; t < kBinTiles; ++t) s[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(aj, bi[t], ci[t], 0, 0, 0);
 #pragma unroll
-    for (int k = 0; k < 3 * kBinBatch; ++k) cj[k] = xj[k];
-#pragma unroll
-    for (int k = 0; k < kBinBatch; ++k) {
-      const PairWords p =
-          pair_words<MASKED>(s[k], k, lane_base, bin_bytes, j1 - j, diag ? i - j : -1, sg.win0, sg.bins, spare);
-      __builtin_amdgcn_sched_barrier(0);
-      if (k == kBinBatch - 1) {
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-        __builtin_amdgcn_sched_barrier(0);
+    for (int t = 0; t < kBinTiles; ++t) {
+      if (MASKED && i0 + 16 * t >= sg.na) break;
+      const PairWords p = pair_words(s[t]);
+      uint32_t at;
+      if (MASKED) {
+        const int i = i0 + 16 * t + li, jj = j + lk;
+        const uint32_t bin = p.bin - static_cast<uint32_t>(sg.win0);
+        const bool use = i < sg.na && jj < j1 && (!diag || jj > i) && bin < static_cast<uint32_t>(sg.bins);
+        at = use ? __umul24(bin, bin_bytes) + lane_base : spare;
+      } else {
+        at = __umul24(p.bin, bin_bytes) + lane_base;
       }
-      deposit(hb, p);
+      __builtin_amdgcn_sched_barrier(0);
+      deposit(hb + at, p);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -331,16 +341,14 @@ __global__ __launch_bounds__(kBinThreads) void k_bins(BinArgs b) {
         const int span = kWave / b.sub;
         const int j0 = jt * kWave + sub * span;
         const int j1 = min(sg.nb, j0 + span);
-        const int i = it * kWave + lane;
         const uint32_t bin_bytes = 24u << logR;
         const uint32_t lane_base = static_cast<uint32_t>(lds) * bin_bytes + 24u * (lane & ((1 << logR) - 1));
         auto* hb = reinterpret_cast<unsigned char*>(h);
-        if (i < sg.na) {
-          if (windowed || (diag && it == jt) || (j1 - j0) % kBinBatch)
-            sweep<true>(b.xs, hb, sg, i, j0, j1, diag, lane_base, bin_bytes);
-          else
-            sweep<false>(b.xs, hb, sg, i, j0, j1, false, lane_base, bin_bytes);
-        }
+        const int i0 = it * kWave;
+        if (windowed || (diag && it == jt) || (j1 - j0) % 4 || i0 + kWave > sg.na)
+          sweep<true>(b.xs, b.ld, hb, sg, i0, j0, j1, diag, lane_base, bin_bytes);
+        else
+          sweep<false>(b.xs, b.ld, hb, sg, i0, j0, j1, false, lane_base, bin_bytes);
       }
       // (a type pair with few items cannot fill a bin's fields)
       if (big && round + kBinWaves < wend) {
@@ -364,9 +372,6 @@ hipError_t launch_bins(const BinArgs& b, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// The final sums.
-// ---------------------------------------------------------------------------
 // Roots of P_6 (Gauss-Legendre nodes), and the coefficient of v^k in the
 // Lagrange polynomial of node j as kBinL[k][j] (fit_bins.py prints both).
 __constant__ double kBinNode[kBinMoments] = {-0x1.dd6ca4e80a01ep-1, -0x1.528a09655c95ep-1, -0x1.e8b12d03675c5p-3,
@@ -385,6 +390,265 @@ __constant__ double kBinL[kBinMoments][kBinMoments] = {
     {-0x1.86c7d2f9ece58p+0, 0x1.2667a539aebf1p+2, -0x1.b205245a3fbddp+2, 0x1.b205245a3fbddp+2, -0x1.2667a539aebf1p+2,
      0x1.86c7d2f9ece58p+0}};
 
+// ---------------------------------------------------------------------------
+// Coordinate gradient.  dL/dx_i = sum_j H_ab(r_ij) (x_i - x_j) with
+//     H_ab(r) = sum_m 2 w_m f_a f_b q_m^2 k(q_m r),  k(x) = (cos x - sinc x) / x^2,
+// again an entire function of r^2 per type pair: it is evaluated in FP64 at
+// the six nodes of each bin, kept as a polynomial of degree five in u with FP32
+// coefficients, and read back per pair.
+// ---------------------------------------------------------------------------
+// k(x) = sinc'(x) / x for x >= 0.
+__device__ __forceinline__ double sinc_slope(double x, double ix) {
+  const SinCos t = sincos_any(x);
+  const double far = (t.c - t.s * ix) * ix * ix;
+  const double y = x * x;  // (series below 1/4, where the difference cancels)
+  double near = fma(y, 1.0 / 3991680.0, -1.0 / 45360.0);
+  near = fma(near, -y, -1.0 / 840.0);
+  near = fma(near, y, 1.0 / 30.0);
+  near = fma(near, y, -1.0 / 3.0);
+  return x < 0.25 ? near : far;
+}
+
+// One work-group (four waves): kFieldBins bins, TPG type pairs from
+// blockIdx.y * TPG.  The lanes hold the nodes, the waves take every fourth q.
+template <int TPG>
+__global__ __launch_bounds__(256) void k_bins_field(BinArgs b, const float* __restrict__ table,
+                                                    const double* __restrict__ w, int32_t Nq, double q0, double dq,
+                                                    const double* __restrict__ qdev) {
+  __shared__ double W[kWave][TPG];
+  __shared__ double Q[kWave], iQ[kWave];
+  __shared__ double F[4][TPG][kWave];
+  if (!b.meta->grad) return;
+  const int nbins = b.nbins[0];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int tp0 = blockIdx.y * TPG, ntp = min(TPG, b.TP - tp0);
+  for (int bin0 = blockIdx.x * kFieldBins; bin0 < nbins; bin0 += gridDim.x * kFieldBins) {
+    const int node = min(lane, kFieldBins * kBinMoments - 1);
+    const double r = bin_node_radius(bin0 + node / kBinMoments, kBinNode[node % kBinMoments]) / b.invh;
+    const double ir = 1.0 / r;
+    double acc[TPG];
+#pragma unroll
+    for (int k = 0; k < TPG; ++k) acc[k] = 0.0;
+    for (int m0 = 0; m0 < Nq; m0 += kWave) {
+      const int nm = min(kWave, Nq - m0);
+      __syncthreads();
+      for (int x = tid; x < kWave * TPG; x += 256) {
+        const int ml = x % kWave, k = x / kWave, m = m0 + ml;
+        double v = 0.0;
+        if (ml < nm && k < ntp) {
+          int ta, tb;
+          tri_decode(tp0 + k, &ta, &tb);
+          const double q = qdev ? qdev[m] : q0 + m * dq;
+          const double fa = table[static_cast<int64_t>(ta) * Nq + m], fb = table[static_cast<int64_t>(tb) * Nq + m];
+          v = 2.0 * w[m] * fa * fb * q * q;
+          if (k == 0) {
+            Q[ml] = q;
+            iQ[ml] = q > 0.0 ? 1.0 / q : 0.0;
+          }
+        }
+        W[ml][k] = v;
+      }
+      __syncthreads();
+      for (int ml = wave; ml < nm; ml += 4) {
+        const double f = sinc_slope(Q[ml] * r, iQ[ml] * ir);
+#pragma unroll
+        for (int k = 0; k < TPG; ++k) acc[k] = fma(W[ml][k], f, acc[k]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < TPG; ++k) F[wave][k][lane] = acc[k];
+    __syncthreads();
+    for (int x = tid; x < kFieldBins * TPG; x += 256) {
+      const int bl = x % kFieldBins, k = x / kFieldBins, bin = bin0 + bl;
+      if (k >= ntp || bin >= nbins) continue;
+      double f[kBinMoments], c[kBinMoments];
+#pragma unroll
+      for (int j = 0; j < kBinMoments; ++j) {
+        const int nd = bl * kBinMoments + j;
+        f[j] = ((F[0][k][nd] + F[1][k][nd]) + F[2][k][nd]) + F[3][k][nd];
+      }
+#pragma unroll
+      for (int p = 0; p < kBinMoments; ++p) {
+        double v = 0.0;
+#pragma unroll
+        for (int j = 0; j < kBinMoments; ++j) v = fma(kBinL[p][j], f[j], v);
+        c[p] = v;
+      }
+      // from powers of v = u + al to powers of u
+      const double al = -0.25 / (bin + 0.5);
+#pragma unroll
+      for (int pass = 0; pass < kBinMoments - 1; ++pass)
+#pragma unroll
+        for (int p = kBinMoments - 2; p >= pass; --p) c[p] = fma(al, c[p + 1], c[p]);
+      float* to = b.field + (static_cast<int64_t>(tp0 + k) * nbins + bin) * kBinMoments;
+#pragma unroll
+      for (int p = 0; p < kBinMoments; ++p) to[p] = static_cast<float>(c[p]);
+    }
+  }
+}
+
+// One unit per work-group: 64 atoms of type a, the 16 waves sweeping their
+// parts of the unit's atoms of type b.  Per pair the distance, bin and u as in
+// the profile, six coefficients from LDS and a Horner scheme in FP32; the sums
+// of H and H x_j over the swept atoms are FP64 products on the matrix cores
+// (v_mfma_f64_4x4x4 again: H in the layout its own distances left), so that
+// x_i - x_j is never formed: x_i sum H - sum H x_j has its common part cancel
+// in FP64.
+template <bool MASKED>
+__device__ __forceinline__ void sweep_grad(const double* __restrict__ xs, int64_t ld, const unsigned char* hb, int b0,
+                                           int j0, int j1, const double (&bi)[kBinTiles], const double (&ci)[kBinTiles],
+                                           uint32_t lane_base, uint32_t bin_bytes, double (&g)[kBinTiles]) {
+  const int lane = threadIdx.x % kWave, lk = lane / 16, lc = lane % 4;
+  const double* pa = xs + lk * ld + b0;            // component lk of atom j + lane % 4
+  const double* px = xs + min(lc, 2) * ld + b0;    // component lane % 4 (3: one) of atom j + lk
+  auto load = [&](int j, double* a, double* x) {
+    const int ja = MASKED ? min(j + lc, j1 - 1) : j + lc, jx = MASKED ? min(j + lk, j1 - 1) : j + lk;
+    *a = pa[ja];
+    *x = px[jx];
+  };
+  double an, xn;
+  load(j0, &an, &xn);
+#pragma unroll 1
+  for (int j = j0; j < j1; j += 4) {
+    const double aj = an, xj = lc == 3 ? 1.0 : xn;
+    load(j + 4 < j1 ? j + 4 : j, &an, &xn);
+    double s[kBinTiles];
+#pragma unroll
+    for (int t = 0; t < kBinTiles; ++t) s[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(aj, bi[t], ci[t], 0, 0, 0);
+    float u[kBinTiles], h[kBinTiles];
+    float2 c0[kBinTiles], c1[kBinTiles], c2[kBinTiles];
+#pragma unroll
+    for (int t = 0; t < kBinTiles; ++t) {
+      float fb;
+      u[t] = pair_coordinate(s[t], &fb);
+      const auto* at = reinterpret_cast<const float2*>(hb + (__umul24(static_cast<uint32_t>(fb), bin_bytes) + lane_base));
+      c0[t] = at[0];
+      c1[t] = at[1];
+      c2[t] = at[2];
+    }
+#pragma unroll
+    for (int t = 0; t < kBinTiles; ++t) {
+      float v = fmaf(c2[t].y, u[t], c2[t].x);
+      v = fmaf(v, u[t], c1[t].y);
+      v = fmaf(v, u[t], c1[t].x);
+      v = fmaf(v, u[t], c0[t].y);
+      v = fmaf(v, u[t], c0[t].x);
+      h[t] = MASKED && j + lk >= j1 ? 0.f : v;
+    }
+#pragma unroll
+    for (int t = 0; t < kBinTiles; ++t)
+      g[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(static_cast<double>(h[t]), xj, g[t], 0, 0, 0);
+  }
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_bins_grad(BinArgs b) {
+  __shared__ float2 h[kBinCap * 3];
+  __shared__ int32_t below;
+  if (!b.meta->grad) return;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int64_t unit = blockIdx.x;
+  const int E = b.T * b.T;
+  if (unit >= b.gents[E].unit0) return;
+  if (tid == 0) below = 0;
+  __syncthreads();
+  {
+    int mine = 0;
+    for (int e = tid; e < E; e += kBinThreads) mine += b.gents[e].unit0 <= unit;
+    for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_down(mine, off, kWave);
+    if (lane == 0) atomicAdd(&below, mine);
+  }
+  __syncthreads();
+  const GradEntry en = b.gents[below - 1];
+  const int k = static_cast<int>(unit - en.unit0);
+  const int tile = k / en.chunks, chunk = k - tile * en.chunks;
+  const int i0 = tile * kWave;
+  const int c0 = chunk * b.span, c1 = min(en.nb, c0 + b.span);
+  // the type pair's table, in as many copies as help (consecutive lanes read
+  // different ones): the pairs of a unit must pay for filling them
+  const int nbins = b.nbins[0];
+  int logR = 0;
+  while (logR < 4 && (nbins << (logR + 1)) <= kBinCap && (nbins << (logR + 1)) * 2 <= c1 - c0) ++logR;
+  const float2* field = reinterpret_cast<const float2*>(b.field + static_cast<int64_t>(en.tp) * nbins * kBinMoments);
+  for (int x = tid; x < (nbins * 3) << logR; x += kBinThreads) {
+    const int row = x / 3, part = x - row * 3;
+    h[x] = field[(row >> logR) * 3 + part];
+  }
+  const int li = lane % 16, lk = lane / 16;
+  double bi[kBinTiles], ci[kBinTiles], g[kBinTiles];
+#pragma unroll
+  for (int t = 0; t < kBinTiles; ++t) {
+    const int64_t at = en.a0 + min(i0 + 16 * t + li, en.na - 1);
+    const double x = b.xs[lk * b.ld + at];
+    bi[t] = lk == 3 ? 1.0 : -2.0 * x;
+    ci[t] = b.xs[3 * b.ld + at];
+    g[t] = 0.0;
+  }
+  __syncthreads();
+  const int each = (((c1 - c0) + kBinWaves - 1) / kBinWaves + 3) / 4 * 4;
+  const int j0 = c0 + wave * each, j1 = min(c1, j0 + each);
+  const uint32_t bin_bytes = 24u << logR;
+  const uint32_t lane_base = 24u * (lane & ((1 << logR) - 1));
+  const auto* hb = reinterpret_cast<const unsigned char*>(h);
+  if (j0 < j1) {
+    if ((j1 - j0) % 4)
+      sweep_grad<true>(b.xs, b.ld, hb, en.b0, j0, j1, bi, ci, lane_base, bin_bytes, g);
+    else
+      sweep_grad<false>(b.xs, b.ld, hb, en.b0, j0, j1, bi, ci, lane_base, bin_bytes, g);
+  }
+  // the waves' sums in order; lane l of tile t holds component l % 4 of atom
+  // 16 t + 4 ((l / 4) % 4) + l / 16
+  __syncthreads();
+  double* red = reinterpret_cast<double*>(h);
+#pragma unroll
+  for (int t = 0; t < kBinTiles; ++t) red[(wave * kBinTiles + t) * kWave + lane] = g[t];
+  __syncthreads();
+  if (tid < kBinTiles * kWave) {
+    double v = 0.0;
+    for (int x = 0; x < kBinWaves; ++x) v += red[x * kBinTiles * kWave + tid];
+    const int t = tid / kWave, l = tid % kWave;
+    b.gpart[(unit * kWave + 16 * t + 4 * ((l / 4) % 4) + l / 16) * 4 + l % 4] = v;
+  }
+}
+
+// Four lanes per atom: the units of its tile, in order, one component each.
+__global__ __launch_bounds__(256) void k_bins_grad_final(BinArgs b, const int32_t* __restrict__ toff, int32_t n,
+                                                         double* __restrict__ grad_out) {
+  if (!b.meta->grad) return;
+  const int at = static_cast<int>(blockIdx.x * 64 + threadIdx.x / 4), c = threadIdx.x % 4;
+  double v = 0.0;
+  if (at < n) {
+    int ta = 0;
+    while (ta + 1 < b.T && toff[ta + 1] <= at) ++ta;
+    const int local = at - toff[ta], tile = local / kWave, row = local % kWave;
+    for (int tb = 0; tb < b.T; ++tb) {
+      const GradEntry en = b.gents[ta * b.T + tb];
+      const double* p = b.gpart + ((en.unit0 + static_cast<int64_t>(tile) * en.chunks) * kWave + row) * 4 + c;
+#pragma unroll 4
+      for (int k = 0; k < en.chunks; ++k) v += p[static_cast<int64_t>(k) * kWave * 4];
+    }
+  }
+  const double sum = __shfl(v, (threadIdx.x % kWave) | 3, kWave);  // sum of H
+  if (at < n && c < 3) grad_out[3 * static_cast<int64_t>(b.order[at]) + c] = (b.xs[c * b.ld + at] * sum - v) / b.invh;
+}
+
+hipError_t launch_bins_grad(const BinArgs& b, int64_t n, int64_t max_units, const float* table, const double* w,
+                            int32_t Nq, double q0, double dq, const double* qdev, double* grad_out, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const uint32_t groups = 160;  // (a molecule of more bins goes round)
+  if (b.TP == 1)
+    hipLaunchKernelGGL(k_bins_field<1>, dim3(groups, 1), dim3(256), 0, st, b, table, w, Nq, q0, dq, qdev);
+  else
+    hipLaunchKernelGGL(k_bins_field<8>, dim3(groups, (b.TP + 7) / 8), dim3(256), 0, st, b, table, w, Nq, q0, dq, qdev);
+  hipLaunchKernelGGL(k_bins_grad, dim3(static_cast<uint32_t>(max_units)), dim3(kBinThreads), 0, st, b);
+  hipLaunchKernelGGL(k_bins_grad_final, dim3(static_cast<uint32_t>(ceil_div(n, 64))), dim3(256), 0, st, b, b.toff,
+                     static_cast<int32_t>(n), grad_out);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// The final sums.
+// ---------------------------------------------------------------------------
 // sin(x) / x for 0 <= x < 1.6e6, given 1/x (any finite value at x = 0).
 __device__ __forceinline__ double sinc_f64(double x, double ix) {
   const double v = sincos_any(x).s * ix;

@@ -32,8 +32,9 @@ constexpr int kBinMaxWindows = 4;     // windows a distance range may take befor
 constexpr int kBinMaxTypes = 64;      // T (type pairs: T (T + 1) / 2)
 constexpr int kBinThreads = 1024;     // one work-group per CU
 constexpr int kBinWaves = kBinThreads / kWave;
-constexpr int kBinPad = 8;            // rows past the last atom that a batch may read
+constexpr int kBinPad = 80;           // rows past the last atom that an item may read
 constexpr int kBinSegs = 64;          // (structure, type pair) sums a work-group keeps at a time
+constexpr int kFieldBins = 10;        // bins per work-group of the force tables (60 nodes)
 constexpr int kBinChunk = 8;          // bins turned into nodes at a time by the final sums
 
 // One (structure, type pair): rows of the two type segments (lane side a, swept
@@ -49,22 +50,34 @@ struct BinEntry {
   int32_t pad;
 };
 
+// Coordinate gradient: one ordered pair of types.  A unit is 64 atoms of a by
+// up to `span` atoms of b.
+struct GradEntry {
+  int64_t unit0;   // first unit; tile t's chunk c is unit0 + t * chunks + c
+  int32_t a0, na;
+  int32_t b0, nb;
+  int32_t tp;      // the type pair's table
+  int32_t chunks;  // of the swept segment
+};
+
 // Device-side results of the planning step.
 struct BinMeta {
   int64_t items;      // total work items
   int64_t pool_used;  // bins in use
   int32_t fallback;   // structures left to the recurrence or direct form
-  int32_t pad;
+  int32_t grad;       // 1: the coordinate gradient is binned
 };
 
 struct BinArgs {
   int32_t on;              // 0: this call does not use the binned form
   int32_t S, T, TP;        // structures, types, type pairs
-  int32_t sub;             // items per 64-atom tile of the swept side (1, 2, 4 or 8)
+  int32_t sub;             // items per 64-atom tile of the swept side (1, 2 or 4)
   int32_t max_bins;        // bins a structure may take (windows included)
   int64_t pool_cap;        // bins the pool holds
   double invh;             // qmax / kBinStep
-  double* xs;              // [atoms + kBinPad][3] sorted coordinates times invh
+  double* xs;              // [4][ld] coordinates (centred, times invh) and their square, in the binned order
+  int64_t ld;              // atoms + kBinPad
+  double* centre;          // [S][3] of the bounding boxes
   const int32_t* toff;     // [S][T + 1] absolute start of each type segment
   float* bbox;             // [pack blocks][6] lower and upper corners
   int32_t* nbins;          // [S]
@@ -80,6 +93,12 @@ struct BinArgs {
   int32_t Nq;
   int32_t pair_wgs;        // work-groups of the pair kernel
   double alt_steps;        // steps per pair of the form it replaces
+  // coordinate gradient (one structure)
+  int32_t span;            // swept atoms per unit; 0: no gradient
+  GradEntry* gents;        // [T * T + 1]
+  int32_t* order;          // [atoms] caller's index of each place of the binned order
+  float* field;            // [TP][bins][kBinMoments] the pair force as a polynomial in u
+  double* gpart;           // [units][64][4] sums of H x_j, H y_j, H z_j, H
 };
 
 // Fixed point.  A pair adds three 64-bit words per bin: count | u, u^5 | u^2,
@@ -123,6 +142,11 @@ constexpr int kBinGroups = 64;
 
 hipError_t launch_bins_plan(const BinArgs& b, const DescView& sd, const int32_t* toff, hipStream_t st);
 hipError_t launch_bins(const BinArgs& b, hipStream_t st);
+// Coordinate gradient from the same bins: the pair force tables, the sums over
+// pairs (max_units: at least the plan's unit count) and the result in the
+// caller's order.
+hipError_t launch_bins_grad(const BinArgs& b, int64_t n, int64_t max_units, const float* table, const double* w,
+                            int32_t Nq, double q0, double dq, const double* qdev, double* grad_out, hipStream_t st);
 // The final sums of the binned structures, and the slice sums of the others.
 hipError_t launch_bins_reduce(const BinArgs& b, const DescView& sd, int64_t n_slices, const double* partial,
                               double* slices, const int32_t* toff, const float* table, int32_t Nq, double q0, double dq,

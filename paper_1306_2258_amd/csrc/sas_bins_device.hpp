@@ -134,6 +134,39 @@ __device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int
     b.entries[E] = end;
     b.meta->items = items;
   }
+  if (b.span <= 0) return;
+  // gradient: ordered pairs of types (one structure); its tables hold one window
+  const bool on = b.route[0] && b.nbins[0] <= kBinCap;
+  int64_t units = 0;
+  for (int x0 = 0; x0 < b.T * b.T; x0 += 256) {
+    const int x = x0 + threadIdx.x;
+    GradEntry en{};
+    int64_t count = 0;
+    if (x < b.T * b.T) {
+      const int ta = x / b.T, tb = x - ta * b.T;
+      const int lo = min(ta, tb), hi = max(ta, tb);
+      en.a0 = toff[ta];
+      en.na = toff[ta + 1] - en.a0;
+      en.b0 = toff[tb];
+      en.nb = toff[tb + 1] - en.b0;
+      en.tp = hi * (hi + 1) / 2 + lo;
+      en.chunks = (en.nb + b.span - 1) / b.span;
+      count = on ? static_cast<int64_t>((en.na + kWave - 1) / kWave) * en.chunks : 0;
+    }
+    int64_t sum = 0;
+    const int64_t incl = scan256(count, &sum);
+    if (x < b.T * b.T) {
+      en.unit0 = units + incl - count;
+      b.gents[x] = en;
+    }
+    units += sum;
+  }
+  if (threadIdx.x == 0) {
+    GradEntry end{};
+    end.unit0 = units;
+    b.gents[b.T * b.T] = end;
+    b.meta->grad = on ? 1 : 0;
+  }
 }
 
 // Centre and half width of bin b in t^2 are b^2 + b + 1/2 and b + 1/2: the

@@ -173,6 +173,7 @@ __global__ __launch_bounds__(256) void k_pack_scan(DescView sd, int32_t T, int32
       const float hi = fmaxf(fmaxf(ext[0][c + 3], ext[1][c + 3]), fmaxf(ext[2][c + 3], ext[3][c + 3]));
       const double x = d.n > 0 ? static_cast<double>(hi) - static_cast<double>(lo) : 0.0;
       sq = fma(x, x, sq);
+      bins.centre[3 * static_cast<int64_t>(s) + c] = d.n > 0 ? 0.5 * (static_cast<double>(hi) + static_cast<double>(lo)) : 0.0;
     }
     bins.nbins[s] = bin_count(bins, sqrt(sq), d.n);
   }
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __rest
                                                              int32_t* __restrict__ perm, BinArgs bins) {
   __shared__ int32_t ty[kPackBlock];
   const int64_t b = blockIdx.x;
-  if (bins.on) {  // clear the sums of the bins in use
+  if (bins.on && bins.pool) {  // clear the sums of the bins in use
     const int64_t words = bins.meta->pool_used * kBinMoments, stride = static_cast<int64_t>(gridDim.x) * kPackBlock;
     for (int64_t k = b * kPackBlock + threadIdx.x; k < words; k += stride) bins.pool[k] = 0;
   }
@@ -208,10 +209,15 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __rest
   xyz[dest] = make_double4(x, y, z, 0.0);
   if (bins.on) {
     const int32_t* o = bins.toff + static_cast<int64_t>(s) * (T + 1) + t;
-    double* to = bins.xs + 3 * (o[0] + bin_spread(static_cast<int32_t>(dest - o[0]), o[1] - o[0]));
-    to[0] = x * bins.invh;
-    to[1] = y * bins.invh;
-    to[2] = z * bins.invh;
+    const double* c = bins.centre + 3 * static_cast<int64_t>(s);
+    const double px = (x - c[0]) * bins.invh, py = (y - c[1]) * bins.invh, pz = (z - c[2]) * bins.invh;
+    const int64_t at = o[0] + bin_spread(static_cast<int32_t>(dest - o[0]), o[1] - o[0]);
+    if (bins.span > 0) bins.order[at] = static_cast<int32_t>(src);
+    double* to = bins.xs + at;
+    to[0] = px;
+    to[bins.ld] = py;
+    to[2 * bins.ld] = pz;
+    to[3 * bins.ld] = fma(pz, pz, fma(py, py, px * px));
   }
   tsort[dest] = t;
   perm[dest] = static_cast<int32_t>(src);

@@ -91,7 +91,7 @@ struct AdjArgs {
   int64_t n_strips;
   double q0, dq;
   const double* qdev;   // non-null: arbitrary grid [Nq] on the device (direct variant)
-  const int32_t* route; // non-null: [0] = 1 when the binned form does the work
+  const int32_t* binned; // non-null: 1 when the binned form does the work
 };
 
 struct BinArgs;  // the binned form (sas_bins.hpp)
