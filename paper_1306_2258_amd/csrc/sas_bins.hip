@@ -115,32 +115,33 @@ __device__ __forceinline__ void empty_bins(unsigned long long* h, const BinSeg* 
 using SumWord = unsigned long long;
 
 struct PairWords {
-  uint32_t bin, f1, f2, f3, f4, f5;
+  uint32_t bin;  // in the low 24 bits
+  uint32_t f1, f2, f3, f4, f5;
 };
 
-// u of a pair and its bin (as a float) from the square s.
-__device__ __forceinline__ float pair_coordinate(double s, float* bin) {
-  // (s may come out a little below zero for atoms that coincide)
-  const float fb = __builtin_truncf(__builtin_amdgcn_sqrtf(fabsf(static_cast<float>(s))));
-  const float tc = fb + 0.5f;
+// u of a pair and its bin from S = s + 1/4.  Adding 2^23 - 1/2 to the root (at
+// least 1/2) rounds it to the bin's number plus 2^23, which leaves the number
+// in the sum's low 24 bits; taking it off again leaves the bin's centre.
+__device__ __forceinline__ float pair_coordinate(double s, uint32_t* bin) {
+  constexpr float kRound = 0x1.fffffep+22f;
+  const float x = __builtin_amdgcn_sqrtf(static_cast<float>(s)) + kRound;
+  const float tc = x - kRound;
   const double tcd = static_cast<double>(tc);
   const float d = static_cast<float>(fma(-tcd, tcd, s));
-  *bin = fb;
+  *bin = __float_as_uint(x);
   return d * __builtin_amdgcn_rcpf(tc);
 }
 
 __device__ __forceinline__ PairWords pair_words(double s) {
   const float magic = 0x1.8p+23f;
   PairWords p;
-  float fb;
-  const float u = pair_coordinate(s, &fb);
+  const float u = pair_coordinate(s, &p.bin);
   const float u2 = u * u, u3 = u2 * u, u4 = u2 * u2, u5 = u4 * u;
   p.f1 = __float_as_uint(fmaf(u, static_cast<float>(1 << kBinBits1), magic));
   p.f2 = __float_as_uint(fmaf(u2, static_cast<float>(1 << kBinBits2), magic));
   p.f3 = __float_as_uint(fmaf(u3, static_cast<float>(1 << kBinBits3), magic));
   p.f4 = __float_as_uint(fmaf(u4, static_cast<float>(1 << kBinBits4), magic)) << kBinShift4;
   p.f5 = __float_as_uint(fmaf(u5, static_cast<float>(1 << kBinBits5), magic)) << kBinShift5;
-  p.bin = static_cast<uint32_t>(fb);
   return p;
 }
 
@@ -174,7 +175,7 @@ __device__ __forceinline__ void sweep(const double* __restrict__ xs, int64_t ld,
     const int64_t at = sg.a0 + i0 + 16 * t + li;
     const double x = xk[at];
     bi[t] = lk == 3 ? 1.0 : -2.0 * x;
-    ci[t] = xs[3 * ld + at];
+    ci[t] = xs[3 * ld + at] + 0.25;
   }
   const uint32_t spare = 24u * (kBinCap + lane);
   double next = *pj;
@@ -193,7 +194,7 @@ __device__ __forceinline__ void sweep(const double* __restrict__ xs, int64_t ld,
       uint32_t at;
       if (MASKED) {
         const int i = i0 + 16 * t + li, jj = j + lk;
-        const uint32_t bin = p.bin - static_cast<uint32_t>(sg.win0);
+        const uint32_t bin = (p.bin & 0xffffffu) - static_cast<uint32_t>(sg.win0);
         const bool use = i < sg.na && jj < j1 && (!diag || jj > i) && bin < static_cast<uint32_t>(sg.bins);
         at = use ? __umul24(bin, bin_bytes) + lane_base : spare;
       } else {
@@ -257,9 +258,18 @@ __global__ __launch_bounds__(kBinThreads) void k_bins(BinArgs b) {
         const int32_t y = __shfl_up(sum, off, kWave);
         if (lane >= off) sum += y;
       }
-      // the pass ends before the first type pair that does not fit, and after
+      // the pass ends before the first type pair that does not fit, or that would
+      // cost the bins their copies once there are rounds enough, and after
       // a window of a split one (whose other windows come in later passes)
-      const unsigned long long over = __ballot(sum > kBinCap);
+      int64_t before = live ? s1 - s0 : 0;
+      const int64_t own = before;
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int64_t y = __shfl_up(before, off, kWave);
+        if (lane >= off) before += y;
+      }
+      before -= own;  // items of the type pairs before this one
+      const unsigned long long over =
+          __ballot(sum > kBinCap || ((sum << kBinMaxCopies) > kBinCap && before >= 8 * kBinWaves));
       const unsigned long long cuts = __ballot(split);
       int n = over ? __ffsll(over) - 1 : kWave;
       if (cuts) n = min(n, static_cast<int>(__ffsll(cuts)));
@@ -296,7 +306,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bins(BinArgs b) {
         nseg_s = __popcll(used);
         bins_s = tot;
         end_s = last;
-        big_s = most * kWave * (kWave / b.sub) > kBinMaxCount;
+        big_s = most * kWave * (kWave / b.sub) > kBinMaxCount;  // (one copy; more have room to spare)
       }
     }
     __syncthreads();
@@ -308,12 +318,13 @@ __global__ __launch_bounds__(kBinThreads) void k_bins(BinArgs b) {
     // banks, as long as they fit and the pairs pay for emptying them
     int logR = 0;
     const int64_t pairs = (wend - w) * kWave * (kWave / b.sub);
-    while (logR < 4 && (static_cast<int64_t>(nbins) << (logR + 1)) <= kBinCap &&
+    while (logR < kBinMaxCopies && (static_cast<int64_t>(nbins) << (logR + 1)) <= kBinCap &&
            (static_cast<int64_t>(nbins) << (logR + 1)) * 16 <= pairs)
       ++logR;
     for (int k = tid; k < (nbins * 3) << logR; k += kBinThreads) h[k] = 0;
     __syncthreads();
     const int64_t seg_first = lane < nseg ? seg[lane].item0 : INT64_MAX;
+    int unchecked = 0;
     for (int64_t round = w; round < wend; round += kBinWaves) {
       const int64_t item = round + wave;
       if (item < wend) {
@@ -350,8 +361,10 @@ __global__ __launch_bounds__(kBinThreads) void k_bins(BinArgs b) {
         else
           sweep<false>(b.xs, b.ld, hb, sg, i0, j0, j1, false, lane_base, bin_bytes);
       }
-      // (a type pair with few items cannot fill a bin's fields)
-      if (big && round + kBinWaves < wend) {
+      // (a type pair with few items cannot fill a bin's fields; each copy takes
+      // its lanes' share of a round's pairs)
+      if (big && ++unchecked == 1 << logR && round + kBinWaves < wend) {
+        unchecked = 0;
         __syncthreads();
         empty_bins(h, seg, nseg, nbins, logR, kBinSpill, b.pool);
         __syncthreads();
@@ -474,12 +487,15 @@ __global__ __launch_bounds__(256) void k_bins_field(BinArgs b, const float* __re
         for (int j = 0; j < kBinMoments; ++j) v = fma(kBinL[p][j], f[j], v);
         c[p] = v;
       }
-      // from powers of v = u + al to powers of u
-      const double al = -0.25 / (bin + 0.5);
+      // from powers of v to powers of u
+      const BinShift sh = bin_shift(bin);
+      double scale = 1.0;
+#pragma unroll
+      for (int p = 1; p < kBinMoments; ++p) c[p] *= (scale *= sh.scale);
 #pragma unroll
       for (int pass = 0; pass < kBinMoments - 1; ++pass)
 #pragma unroll
-        for (int p = kBinMoments - 2; p >= pass; --p) c[p] = fma(al, c[p + 1], c[p]);
+        for (int p = kBinMoments - 2; p >= pass; --p) c[p] = fma(sh.offset, c[p + 1], c[p]);
       float* to = b.field + (static_cast<int64_t>(tp0 + k) * nbins + bin) * kBinMoments;
 #pragma unroll
       for (int p = 0; p < kBinMoments; ++p) to[p] = static_cast<float>(c[p]);
@@ -519,9 +535,9 @@ __device__ __forceinline__ void sweep_grad(const double* __restrict__ xs, int64_
     float2 c0[kBinTiles], c1[kBinTiles], c2[kBinTiles];
 #pragma unroll
     for (int t = 0; t < kBinTiles; ++t) {
-      float fb;
-      u[t] = pair_coordinate(s[t], &fb);
-      const auto* at = reinterpret_cast<const float2*>(hb + (__umul24(static_cast<uint32_t>(fb), bin_bytes) + lane_base));
+      uint32_t bin;
+      u[t] = pair_coordinate(s[t], &bin);
+      const auto* at = reinterpret_cast<const float2*>(hb + (__umul24(bin, bin_bytes) + lane_base));
       c0[t] = at[0];
       c1[t] = at[1];
       c2[t] = at[2];
@@ -568,7 +584,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bins_grad(BinArgs b) {
   // different ones): the pairs of a unit must pay for filling them
   const int nbins = b.nbins[0];
   int logR = 0;
-  while (logR < 4 && (nbins << (logR + 1)) <= kBinCap && (nbins << (logR + 1)) * 2 <= c1 - c0) ++logR;
+  while (logR < kBinMaxCopies && (nbins << (logR + 1)) <= kBinCap && (nbins << (logR + 1)) * 2 <= c1 - c0) ++logR;
   const float2* field = reinterpret_cast<const float2*>(b.field + static_cast<int64_t>(en.tp) * nbins * kBinMoments);
   for (int x = tid; x < (nbins * 3) << logR; x += kBinThreads) {
     const int row = x / 3, part = x - row * 3;
@@ -581,7 +597,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bins_grad(BinArgs b) {
     const int64_t at = en.a0 + min(i0 + 16 * t + li, en.na - 1);
     const double x = b.xs[lk * b.ld + at];
     bi[t] = lk == 3 ? 1.0 : -2.0 * x;
-    ci[t] = b.xs[3 * b.ld + at];
+    ci[t] = b.xs[3 * b.ld + at] + 0.25;
     g[t] = 0.0;
   }
   __syncthreads();
@@ -658,8 +674,8 @@ __device__ __forceinline__ double sinc_f64(double x, double ix) {
 // One work-group (four waves): the groups first, first + b.wgs, ... of a
 // structure for 64 q values, TPG type pairs at a time.  Per node a reduction
 // and a polynomial for the sine (about 35 FP64 instructions) and one FMA per
-// type pair, the weights read from LDS as broadcasts; three nodes in flight
-// per wave hide the sine's serial chain.
+// type pair, the weights read from LDS as broadcasts a node ahead (read where
+// they are used, their latency took four fifths of the time: rod 88 us).
 template <int TPG, bool SPART>
 __device__ void bins_sum(const BinArgs& b, int s, int first, const float* __restrict__ table, int32_t Nq, double q0,
                          double dq, const double* __restrict__ qdev) {
@@ -675,31 +691,34 @@ __device__ void bins_sum(const BinArgs& b, int s, int first, const float* __rest
   const double iq = qm > 0.0 ? 1.0 / qm : 0.0;
   const int chunks = (nbins + kBinChunk - 1) / kBinChunk;
   const int groups = min(kBinGroups, chunks);
+  // form factor products of the type pairs (2 f_a f_b), loaded together
+  double ff[TPG];
+  auto factors = [&](int tp0) {
+    int ta, tb;
+    tri_decode(tp0, &ta, &tb);
+    float fa[TPG], fb[TPG];
+#pragma unroll
+    for (int k = 0; k < TPG; ++k) {
+      const int64_t mc = m < Nq ? m : 0;
+      fa[k] = table[static_cast<int64_t>(min(ta, b.T - 1)) * Nq + mc];
+      fb[k] = table[static_cast<int64_t>(min(tb, b.T - 1)) * Nq + mc];
+      ++ta;
+      if (ta > tb) {
+        ta = 0;
+        ++tb;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < TPG; ++k) ff[k] = 2.0 * static_cast<double>(fa[k]) * static_cast<double>(fb[k]);
+  };
+  const bool single = b.TP <= TPG;
+  if (single) factors(0);
   double sum = 0.0;
   for (int g = first; g < groups; g += b.wgs) {
     double total = 0.0;
     for (int tp0 = 0; tp0 < b.TP; tp0 += TPG) {
       const int ntp = min(TPG, b.TP - tp0);
-      // form factor products of the type pairs (2 f_a f_b), loaded together
-      double ff[TPG];
-      {
-        int ta, tb;
-        tri_decode(tp0, &ta, &tb);
-        float fa[TPG], fb[TPG];
-#pragma unroll
-        for (int k = 0; k < TPG; ++k) {
-          const int64_t mc = m < Nq ? m : 0;
-          fa[k] = table[static_cast<int64_t>(min(ta, b.T - 1)) * Nq + mc];
-          fb[k] = table[static_cast<int64_t>(min(tb, b.T - 1)) * Nq + mc];
-          ++ta;
-          if (ta > tb) {
-            ta = 0;
-            ++tb;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < TPG; ++k) ff[k] = 2.0 * static_cast<double>(fa[k]) * static_cast<double>(fb[k]);
-      }
+      if (!single) factors(tp0);
       double acc[TPG];
 #pragma unroll
       for (int k = 0; k < TPG; ++k) acc[k] = 0.0;
@@ -731,12 +750,26 @@ __device__ void bins_sum(const BinArgs& b, int s, int first, const float* __rest
         }
         if (ch + kBinGroups < chunks) fetch(ch + kBinGroups);
         __syncthreads();
-#pragma unroll 3
-        for (int x = 0; x < kNodes / 4; ++x) {
-          const int nd = 4 * x + wave;
-          const double f = sinc_f64(qm * R[nd], iq * iR[nd]);
+        // (each node's weights are read while the last one's sine runs)
+        double wn[TPG], rn, irn;
+        auto read = [&](int nd) {
 #pragma unroll
-          for (int k = 0; k < TPG; ++k) acc[k] = fma(W[nd][k], f, acc[k]);
+          for (int k = 0; k < TPG; ++k) wn[k] = W[nd][k];
+          rn = R[nd];
+          irn = iR[nd];
+        };
+        read(wave);
+#pragma unroll
+        for (int x = 0; x < kNodes / 4; ++x) {
+          double wc[TPG];
+#pragma unroll
+          for (int k = 0; k < TPG; ++k) wc[k] = wn[k];
+          const double rc = rn, irc = irn;
+          if (x + 1 < kNodes / 4) read(4 * (x + 1) + wave);
+          __builtin_amdgcn_sched_barrier(0);
+          const double f = sinc_f64(qm * rc, iq * irc);
+#pragma unroll
+          for (int k = 0; k < TPG; ++k) acc[k] = fma(wc[k], f, acc[k]);
         }
       }
 #pragma unroll

@@ -3,9 +3,9 @@
 //
 // Every pair's distance is formed in FP64, as in the other forms, but instead
 // of meeting each q the pair is deposited once, as powers of its position
-// inside a narrow bin of the squared distance.  With t = r qmax / kBinStep,
-// bin b holds t in [b, b + 1) and the pair's coordinate is
-//     u = (t^2 - (b + 1/2)^2) / (b + 1/2),  about [-1, 1].
+// inside a narrow bin of the squared distance.  With t = r qmax / kBinStep and
+// S = t^2 + 1/4, bin b holds sqrt(S) in [b, b + 1) and the pair's coordinate is
+//     u = (S - (b + 1/2)^2) / (b + 1/2),  about [-1, 1].
 // Per type pair and bin the sums of u^k, k = 0..5, fix the sum over the bin's
 // pairs of any function of r^2 that a polynomial of degree 5 in u represents
 // over the bin; sinc(q r) is an entire function of r^2 and q r moves by at most
@@ -33,6 +33,7 @@ constexpr int kBinMaxTypes = 64;      // T (type pairs: T (T + 1) / 2)
 constexpr int kBinThreads = 1024;     // one work-group per CU
 constexpr int kBinWaves = kBinThreads / kWave;
 constexpr int kBinPad = 80;           // rows past the last atom that an item may read
+constexpr int kBinMaxCopies = 4;      // log2 of the copies of a bin in LDS
 constexpr int kBinSegs = 64;          // (structure, type pair) sums a work-group keeps at a time
 constexpr int kFieldBins = 10;        // bins per work-group of the force tables (60 nodes)
 constexpr int kBinChunk = 8;          // bins turned into nodes at a time by the final sums

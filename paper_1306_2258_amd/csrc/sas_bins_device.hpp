@@ -169,15 +169,25 @@ __device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int
   }
 }
 
-// Centre and half width of bin b in t^2 are b^2 + b + 1/2 and b + 1/2: the
-// radius (in units of 1 / invh) of the node at v in [-1, 1].
+// Bin b spans [b, b + 1) of sqrt(t^2 + 1/4), so t^2 + 1/4 has its centre at
+// b^2 + b + 1/2 and half width b + 1/2 there; the first bin begins at 1/4, t = 0.
+// The radius (in units of 1 / invh) of the node at v in [-1, 1] over the bin:
 __device__ __forceinline__ double bin_node_radius(int bin, double v) {
   const double c = bin + 0.5;
-  return sqrt(static_cast<double>(bin) * bin + c + c * v);
+  return sqrt(bin == 0 ? 0.375 + 0.375 * v : static_cast<double>(bin) * bin + bin + 0.25 + c * v);
+}
+
+// v over the bin from a pair's u = (t^2 + 1/4 - (b + 1/2)^2) / (b + 1/2):
+// v = scale (u + offset).
+struct BinShift {
+  double scale, offset;
+};
+__device__ __forceinline__ BinShift bin_shift(int bin) {
+  return bin == 0 ? BinShift{4.0 / 3.0, -0.75} : BinShift{1.0, -0.25 / (bin + 0.5)};
 }
 
 // Weights of a bin's six nodes from its integer sums: the sums of u^k, moved to
-// the powers of v = u - 1/(4 (b + 1/2)), which spans [-1, 1] over the bin.
+// the powers of v.
 __device__ __forceinline__ void bin_node_weights(const unsigned long long (&p)[kBinMoments], int bin,
                                                  const double (&L)[kBinMoments][kBinMoments],
                                                  double (&wn)[kBinMoments]) {
@@ -186,12 +196,16 @@ __device__ __forceinline__ void bin_node_weights(const unsigned long long (&p)[k
 #pragma unroll
   for (int k = 0; k < kBinMoments; ++k)
     m[k] = static_cast<double>(static_cast<long long>(p[k])) / static_cast<double>(1ll << kBits[k]);
-  const double al = -0.25 / (bin + 0.5);
+  const BinShift sh = bin_shift(bin);
+  const double al = sh.offset;
   // sums of (u + al)^k by repeated Horner shifts: m_k += al m_{k-1}, from the top
 #pragma unroll
   for (int pass = 1; pass < kBinMoments; ++pass)
 #pragma unroll
     for (int k = kBinMoments - 1; k >= pass; --k) m[k] = fma(al, m[k - 1], m[k]);
+  double scale = 1.0;
+#pragma unroll
+  for (int k = 1; k < kBinMoments; ++k) m[k] *= (scale *= sh.scale);
 #pragma unroll
   for (int j = 0; j < kBinMoments; ++j) {
     double w = 0.0;

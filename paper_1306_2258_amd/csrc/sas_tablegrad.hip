@@ -91,7 +91,10 @@ __global__ __launch_bounds__(256) void k_table_grad_final(int64_t n_slices,
         const int lo = t < b ? t : b, hi = t < b ? b : t;
         const int64_t tp = static_cast<int64_t>(hi) * (hi + 1) / 2 + lo;
         double s = 0.0;
-        for (int k2 = 0; k2 < rows; ++k2) s += bins.spart[(k2 * static_cast<int64_t>(bins.TP) + tp) * Nq + m];
+        const double* p = bins.spart + tp * Nq + m;
+        const int64_t step = static_cast<int64_t>(bins.TP) * Nq;
+#pragma unroll 16
+        for (int k2 = 0; k2 < rows; ++k2) s += p[k2 * step];
         g = fma((b == t ? 2.0 : 1.0) * static_cast<double>(table[static_cast<int64_t>(b) * Nq + m]), s, g);
       }
       grad_table[k] = w[m] * 2.0 * (nt * static_cast<double>(table[k]) + g);
