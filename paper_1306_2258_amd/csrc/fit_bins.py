@@ -5,8 +5,13 @@ replaced by the polynomial through its values at the six Gauss-Legendre nodes
 v_j, the roots of P_6.  Row k, column j of the second table is the coefficient
 of v^k in the Lagrange polynomial of node j.
 
-    python fit_bins.py        # prints both as C initialisers
+The sums are of u^k rounded to fixed point.  Where few bits are left to u^4,
+its many small values round to zero; rounding_mean gives the mean error for u
+uniform on [-1, 1].
+
+    python fit_bins.py        # prints the tables as C initialisers, and the mean
 """
+import math
 from fractions import Fraction
 
 DEGREE = 6
@@ -65,8 +70,18 @@ def lagrange(v):
     return table
 
 
+def rounding_mean(power, bits):
+    """Mean over u in [0, 1] of round(2^bits u^power) / 2^bits - u^power: the
+    integer j is taken between the u where 2^bits u^power is j - 1/2 and j + 1/2."""
+    scale = 2.0 ** bits
+    edge = [((j + 0.5) / scale) ** (1.0 / power) for j in range(2 ** bits)] + [1.0]
+    total = math.fsum(j / scale * (edge[j] - edge[j - 1]) for j in range(1, 2 ** bits + 1))
+    return total - 1.0 / (power + 1)
+
+
 if __name__ == "__main__":
     v = nodes()
     print("{" + ", ".join(float(x).hex() for x in v) + "}")
     for row in lagrange(v):
         print("{" + ", ".join(float(x).hex() for x in row) + "},")
+    print(rounding_mean(4, 10).hex())

@@ -184,7 +184,7 @@ struct Layout {
   size_t gpart = 0, gslices = 0;  // table gradient: [strips][T][Nq], [slices][T][Nq]
   size_t counter = 0;             // persistent launch: the work counter
   // binned form
-  size_t bxs = 0, bcentre = 0, bbox = 0, bnbins = 0, broute = 0, bpooloff = 0, bmeta = 0, bentries = 0, bpool = 0, bpart = 0,
+  size_t bxs = 0, bcentre = 0, bdone = 0, bbox = 0, bnbins = 0, broute = 0, bpooloff = 0, bmeta = 0, bentries = 0, bpool = 0, bpart = 0,
          bspart = 0, bgents = 0, border = 0, bfield = 0, bgpart = 0;
   // host-written block, uploaded in one copy: structure descriptors (S > 1)
   // followed by the q grid (direct form)
@@ -375,7 +375,7 @@ void add_bins(Schedule* sc, const sas_ctx* ctx, const std::vector<int64_t>& size
     if (n > kBinMaxAtoms) return;
     pairs += 0.5 * static_cast<double>(n) * static_cast<double>(n - 1);
   }
-  if (pairs < static_cast<double>(sas::kBinMinPairs) ||
+  if (pairs < static_cast<double>(sc->direct ? sas::kBinMinPairsDirect : sas::kBinMinPairs) ||
       pairs < static_cast<double>(kBinMinPairsEach) * static_cast<double>(S))
     return;
   BinArgs& b = sc->ba;
@@ -387,6 +387,7 @@ void add_bins(Schedule* sc, const sas_ctx* ctx, const std::vector<int64_t>& size
   b.Nq = Nq;
   b.invh = qmax / sas::kBinStep;
   b.alt_steps = direct_steps(Nq, !sc->direct);
+  b.clear_ns = sas::small_pack(sizes[0], static_cast<int32_t>(S), T, sc->ldt) ? sas::kBinClearOneNs : sas::kBinClearNs;
   // items of 64 by 64 atoms, or shorter ones when those would leave CUs idle
   const double tiles = pairs / (64.0 * 64.0);
   b.sub = tiles >= 16384.0 ? 1 : (tiles >= 8192.0 ? 2 : 4);
@@ -402,7 +403,7 @@ void add_bins(Schedule* sc, const sas_ctx* ctx, const std::vector<int64_t>& size
     int64_t lo = sas::kBinFree, hi = b.max_bins;  // the largest count that pays
     while (lo < hi) {
       const int64_t mid = (lo + hi + 1) / 2;
-      if (sas::bin_pays(n, mid, TP, Nq, b.pair_wgs, b.alt_steps))
+      if (sas::bin_pays(n, mid, TP, Nq, b.pair_wgs, b.alt_steps, b.clear_ns))
         lo = mid;
       else
         hi = mid - 1;
@@ -563,6 +564,7 @@ Layout make_layout(const Schedule& sc, int32_t T, int32_t Nq) {
     L.broute = take(sizeof(int32_t) * b.S);
     L.bpooloff = take(sizeof(int64_t) * b.S);
     L.bmeta = take(sizeof(sas::BinMeta));
+    L.bdone = take(sizeof(int32_t) * b.S * ((static_cast<size_t>(Nq) + sas::kWave - 1) / sas::kWave));
     if (b.span > 0) {
       L.bgents = take(sizeof(sas::GradEntry) * (static_cast<size_t>(b.T) * b.T + 1));
       L.border = take(sizeof(int32_t) * sc.n_total);
@@ -635,6 +637,7 @@ BinArgs bins_of(const Schedule& sc, void* ws, const Layout& L) {
   b.route = reinterpret_cast<int32_t*>(w + L.broute);
   b.pool_off = reinterpret_cast<int64_t*>(w + L.bpooloff);
   b.meta = reinterpret_cast<sas::BinMeta*>(w + L.bmeta);
+  b.done = reinterpret_cast<int32_t*>(w + L.bdone);
   b.entries = reinterpret_cast<sas::BinEntry*>(w + L.bentries);
   b.pool = reinterpret_cast<unsigned long long*>(w + L.bpool);
   b.part = reinterpret_cast<double*>(w + L.bpart);

@@ -793,26 +793,57 @@ __device__ void bins_sum(const BinArgs& b, int s, int first, const float* __rest
     __syncthreads();
     sum += ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
     if (b.rows > 1) {
-      if (wave == 0 && m < Nq) b.part[(static_cast<int64_t>(s) * b.rows + g) * Nq + m] = sum;
+      if (wave == 0 && m < Nq)
+        __hip_atomic_store(b.part + (static_cast<int64_t>(s) * b.rows + g) * Nq + m, sum, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
       sum = 0.0;
     }
   }
-  if (b.rows == 1 && wave == 0 && m < Nq) b.part[static_cast<int64_t>(s) * Nq + m] = sum;
+  if (b.rows == 1 && wave == 0 && m < Nq)
+    __hip_atomic_store(b.part + static_cast<int64_t>(s) * Nq + m, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The last of a structure's work-groups to finish (a count per structure and q
+// group) also forms the profile, which spares a kernel: the others' rows are
+// stored and read past the XCDs' own caches.
 template <int TPG, bool SPART>
 __global__ __launch_bounds__(256) void k_bins_sum(BinArgs b, DescView sd, const double* __restrict__ partial,
-                                                  double* __restrict__ slices, const float* __restrict__ table,
-                                                  int32_t Nq, double q0, double dq, const double* __restrict__ qdev) {
+                                                  double* __restrict__ slices, const int32_t* __restrict__ toff,
+                                                  const float* __restrict__ table, int32_t Nq, double q0, double dq,
+                                                  const double* __restrict__ qdev, double* __restrict__ I_out) {
+  __shared__ int32_t last;
   const int64_t nb = static_cast<int64_t>(b.S) * b.wgs;
+  const int tid = threadIdx.x;
+  int s, parts;
   if (blockIdx.x < nb) {
-    const int s = static_cast<int>(blockIdx.x / b.wgs), g = static_cast<int>(blockIdx.x % b.wgs);
-    if (b.route[s]) bins_sum<TPG, SPART>(b, s, g, table, Nq, q0, dq, qdev);
-    return;
+    s = static_cast<int>(blockIdx.x / b.wgs);
+    if (b.route[s]) {
+      bins_sum<TPG, SPART>(b, s, static_cast<int>(blockIdx.x % b.wgs), table, Nq, q0, dq, qdev);
+      parts = b.wgs;
+    } else {
+      // (a structure without strips has no slices either)
+      if (blockIdx.x % b.wgs != 0 || sd.get(s).n_slices > 0) return;
+      parts = 1;
+    }
+  } else {
+    const int64_t sl = blockIdx.x - nb;
+    if (b.meta->fallback == 0) return;
+    s = find_struct_by_slice(sd, sl);
+    if (b.route[s]) return;
+    reduce_slice<true>(sd, sl, partial, Nq, slices);
+    parts = sd.get(s).n_slices;
   }
-  const int64_t sl = blockIdx.x - nb;
-  if (b.meta->fallback == 0 || b.route[find_struct_by_slice(sd, sl)]) return;
-  reduce_slice(sd, sl, partial, Nq, slices);
+  if (!I_out) return;
+  if (tid == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the rows were stored by this wave)
+    last = __hip_atomic_fetch_add(b.done + static_cast<int64_t>(s) * gridDim.y + blockIdx.y, 1, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  const int rows = b.route[s] ? bin_rows(b, b.nbins[s]) : -1;
+  reduce_final<true>(sd, s, blockIdx.y, slices, toff, nullptr, table, b.T, Nq, q0, dq, qdev, I_out, rows,
+                     b.part + static_cast<int64_t>(s) * b.rows * Nq);
 }
 
 hipError_t launch_bins_reduce(const BinArgs& b, const DescView& sd, int64_t n_slices, const double* partial,
@@ -821,7 +852,7 @@ hipError_t launch_bins_reduce(const BinArgs& b, const DescView& sd, int64_t n_sl
   const uint32_t qgroups = static_cast<uint32_t>(ceil_div(Nq, kWave));
   const dim3 grid(static_cast<uint32_t>(static_cast<int64_t>(b.S) * b.wgs + n_slices), qgroups);
   auto go = [&](auto* k) {
-    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, b, sd, partial, slices, table, Nq, q0, dq, qdev);
+    hipLaunchKernelGGL(k, grid, dim3(256), 0, st, b, sd, partial, slices, toff, table, Nq, q0, dq, qdev, I_out);
   };
   // (as many type pairs at a time as there are, to 16: each pass repeats the sines)
   if (b.TP == 1)
@@ -830,8 +861,6 @@ hipError_t launch_bins_reduce(const BinArgs& b, const DescView& sd, int64_t n_sl
     b.spart ? go(&k_bins_sum<6, true>) : go(&k_bins_sum<6, false>);
   else
     b.spart ? go(&k_bins_sum<16, true>) : go(&k_bins_sum<16, false>);
-  if (I_out)
-    return launch_reduce_final(sd, b.S, slices, toff, nullptr, table, b.T, Nq, q0, dq, qdev, &b, I_out, st);
   return hipGetLastError();
 }
 

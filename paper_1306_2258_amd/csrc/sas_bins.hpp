@@ -85,6 +85,7 @@ struct BinArgs {
   int32_t* route;          // [S] 1: binned, 0: left to the other form
   int64_t* pool_off;       // [S]
   BinMeta* meta;
+  int32_t* done;           // [S][ceil(Nq / 64)] finished work-groups of the final sums
   BinEntry* entries;       // [S * TP + 1]
   unsigned long long* pool;  // [bins][kBinMoments], fixed point
   double* part;            // [S][rows][Nq] partial profiles
@@ -94,6 +95,7 @@ struct BinArgs {
   int32_t Nq;
   int32_t pair_wgs;        // work-groups of the pair kernel
   double alt_steps;        // steps per pair of the form it replaces
+  double clear_ns;         // cost of clearing a bin's sums of one type pair
   // coordinate gradient (one structure)
   int32_t span;            // swept atoms per unit; 0: no gradient
   GradEntry* gents;        // [T * T + 1]
@@ -110,13 +112,20 @@ struct BinArgs {
 constexpr int kBinBits1 = 21, kBinBits2 = 17, kBinBits3 = 14, kBinBits4 = 10, kBinBits5 = 7;
 constexpr int kBinShift5 = 4, kBinShift4 = 2;  // left shifts of the upper fields
 constexpr int kBinCountShift = 10;             // the count's place in the upper half of the first word
+// Mean of the rounding of u^4 to kBinBits4 bits over uniform u (small u^4 all
+// round to zero; fit_bins.py prints it): taken off with the count.  Left in, it
+// was most of the error (4,000 atoms: 5e-8 of I at its minima, 5e-9 without).
+constexpr double kBinBias4 = -0x1.2700c58d5cp-17;
 constexpr uint32_t kBinMagicBits = 0x4b400000u;
 constexpr int kBinSpill = 1 << 15;             // bins this full are emptied between rounds
 constexpr int kBinMaxCount = kBinSpill + kBinWaves * kWave * 64;
 
 // The type form's profile of n atoms is binned from this many pairs (measured
 // on MI355X) and q values.
-constexpr int64_t kBinMinPairs = 73536;
+constexpr int64_t kBinMinPairs = 8192;
+// (on a non-uniform grid calls below 302 atoms keep the direct form, the only
+// one with a fixed q chunk to report)
+constexpr int64_t kBinMinPairsDirect = 45450;
 constexpr int32_t kBinMinNq = 8;
 
 // Estimated times in ns of the binned form and of the form it replaces, from
@@ -126,14 +135,18 @@ constexpr int32_t kBinMinNq = 8;
 constexpr double kBinPairNs = 1.5e-3, kBinNodeNs = 1e-2, kBinFlushNs = 4e-2, kBinStepNs = 5.2e-5;
 constexpr int kBinFree = 512;  // bins that are always taken
 
+// Clearing a bin's sums: by many work-groups, or by the one of the small pack.
+constexpr double kBinClearNs = 1e-2, kBinClearOneNs = 0.5;
+
 // Whether a structure of n atoms that spans nbins bins is binned.
 __host__ __device__ inline bool bin_pays(int64_t n, int64_t nbins, int32_t TP, int32_t Nq, int32_t wgs,
-                                         double alt_steps) {
+                                         double alt_steps, double clear_ns) {
   if (nbins <= kBinFree) return true;
   const double pairs = 0.5 * static_cast<double>(n) * static_cast<double>(n - 1);
   const double windows = static_cast<double>((nbins + kBinCap - 1) / kBinCap);
   const double passes = static_cast<double>(wgs + TP);
-  const double binned = pairs * windows * kBinPairNs + static_cast<double>(nbins) * (kBinNodeNs * Nq + kBinFlushNs * passes);
+  const double binned = pairs * windows * kBinPairNs +
+                        static_cast<double>(nbins) * (kBinNodeNs * Nq + kBinFlushNs * passes + clear_ns * TP);
   return binned < pairs * alt_steps * kBinStepNs;
 }
 

@@ -24,7 +24,19 @@ __device__ __forceinline__ int32_t bin_count(const BinArgs& b, double diag, int3
   const double t = diag * b.invh * (1.0 + 1e-6);
   if (!(t < static_cast<double>(b.max_bins - 2))) return 0;
   const int32_t nbins = static_cast<int32_t>(t) + 2;
-  return bin_pays(n, nbins, b.TP, b.Nq, b.pair_wgs, b.alt_steps) ? nbins : 0;
+  return bin_pays(n, nbins, b.TP, b.Nq, b.pair_wgs, b.alt_steps, b.clear_ns) ? nbins : 0;
+}
+
+// Bin count and centre of structure s from its bounding box (one thread).
+__device__ __forceinline__ int32_t bin_bounds(const BinArgs& b, int s, int32_t n, const float (&lo)[3],
+                                           const float (&hi)[3]) {
+  double sq = 0.0;
+  for (int c = 0; c < 3; ++c) {
+    const double l = n > 0 ? static_cast<double>(lo[c]) : 0.0, h = n > 0 ? static_cast<double>(hi[c]) : 0.0;
+    sq = fma(h - l, h - l, sq);
+    b.centre[3 * static_cast<int64_t>(s) + c] = 0.5 * (h + l);
+  }
+  return bin_count(b, sqrt(sq), n);
 }
 
 // Place of atom d of a type segment of n in the binned form's order.  Neighbours
@@ -39,15 +51,30 @@ __device__ __forceinline__ int32_t bin_spread(int32_t d, int32_t n) {
   return col < full ? col * r + row : full * r + (col - full) * (r - 1) + row;
 }
 
+// An atom's place in the binned order: row d of type segment [o0, o1) of
+// structure s, caller's index src.
+__device__ __forceinline__ void bin_store(const BinArgs& b, int s, int32_t o0, int32_t o1, int32_t d, int32_t src,
+                                          double x, double y, double z) {
+  const int64_t at = o0 + bin_spread(d, o1 - o0);
+  if (b.span > 0) b.order[at] = src;
+  const double* c = b.centre + 3 * static_cast<int64_t>(s);
+  const double px = (x - c[0]) * b.invh, py = (y - c[1]) * b.invh, pz = (z - c[2]) * b.invh;
+  double* to = b.xs + at;
+  to[0] = px;
+  to[b.ld] = py;
+  to[2 * b.ld] = pz;
+  to[3 * b.ld] = fma(pz, pz, fma(py, py, px * px));
+}
+
 // Rows of partial profiles a structure's final sums write.
 __device__ __forceinline__ int bin_rows(const BinArgs& b, int32_t nbins) {
   return min(b.rows, (nbins + kBinChunk - 1) / kBinChunk);
 }
 
-// Inclusive scan of v over the 256 threads of a work-group; *sum is the total.
-__device__ __forceinline__ int64_t scan256(int64_t v, int64_t* sum) {
-  __shared__ int64_t tot[4];
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+// Inclusive scan of v over the threads of a work-group; *sum is the total.
+__device__ __forceinline__ int64_t scan_block(int64_t v, int64_t* sum) {
+  __shared__ int64_t tot[16];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave, nw = blockDim.x / kWave;
   for (int off = 1; off < kWave; off <<= 1) {
     const int64_t y = __shfl_up(v, off, kWave);
     if (lane >= off) v += y;
@@ -55,41 +82,22 @@ __device__ __forceinline__ int64_t scan256(int64_t v, int64_t* sum) {
   __syncthreads();
   if (lane == kWave - 1) tot[w] = v;
   __syncthreads();
-  for (int k = 0; k < w; ++k) v += tot[k];
-  *sum = tot[0] + tot[1] + tot[2] + tot[3];
+  int64_t all = 0;
+  for (int k = 0; k < nw; ++k) {
+    if (k < w) v += tot[k];
+    all += tot[k];
+  }
+  *sum = all;
   return v;
 }
 
-// Planning by one work-group of 256 threads, after b.nbins (bins per
-// structure, 0: too many) and the type segments toff are known.
-__device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int32_t* toff) {
-  __shared__ int32_t fallback;
-  if (threadIdx.x == 0) fallback = 0;
-  __syncthreads();
-  int64_t pool = 0;
-  for (int s0 = 0; s0 < b.S; s0 += 256) {
-    const int s = s0 + threadIdx.x;
-    const int32_t nb = s < b.S ? b.nbins[s] : 0;
-    const int64_t want = static_cast<int64_t>(nb) * b.TP;
-    int64_t sum = 0;
-    const int64_t incl = scan256(want, &sum);
-    if (s < b.S) {
-      const int64_t off = pool + incl - want;
-      const bool ok = nb > 0 && off + want <= b.pool_cap;
-      b.pool_off[s] = ok ? off : 0;
-      b.route[s] = ok ? 1 : 0;
-      if (!ok) atomicAdd(&fallback, 1);
-    }
-    pool += sum;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    b.meta->pool_used = pool < b.pool_cap ? pool : b.pool_cap;
-    b.meta->fallback = fallback;
-  }
+// The second half: the work items of every structure's type pairs, and the
+// gradient's units.  nbins0, pool0 and route0 are those of the first structure.
+__device__ inline void plan_items(const BinArgs& b, const int32_t* toff, int32_t nbins0, int64_t pool0,
+                                  int32_t route0) {
   const int E = b.S * b.TP;
   int64_t items = 0;
-  for (int x0 = 0; x0 < E; x0 += 256) {
+  for (int x0 = 0; x0 < E; x0 += blockDim.x) {
     const int x = x0 + threadIdx.x;
     BinEntry en{};
     int64_t count = 0;
@@ -112,16 +120,16 @@ __device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int
         en.b0 = a0;
         en.nb = na;
       }
-      en.nbins = b.nbins[s];
-      en.pool = b.pool_off[s] + static_cast<int64_t>(x - s * b.TP) * en.nbins;
+      en.nbins = s == 0 ? nbins0 : b.nbins[s];
+      en.pool = (s == 0 ? pool0 : b.pool_off[s]) + static_cast<int64_t>(x - s * b.TP) * en.nbins;
       const int64_t tiles = en.diag ? ia * (ia + 1) / 2 : ia * ib;
       en.base = static_cast<int32_t>(tiles * b.sub);
       const int wins = (en.nbins + kBinCap - 1) / kBinCap;
-      const bool any = b.route[s] && en.na > 0 && en.nb > 0 && !(en.diag && en.na < 2);
+      const bool any = (s == 0 ? route0 : b.route[s]) && en.na > 0 && en.nb > 0 && !(en.diag && en.na < 2);
       count = any ? static_cast<int64_t>(en.base) * wins : 0;
     }
     int64_t sum = 0;
-    const int64_t incl = scan256(count, &sum);
+    const int64_t incl = scan_block(count, &sum);
     if (x < E) {
       en.item0 = items + incl - count;
       b.entries[x] = en;
@@ -136,9 +144,9 @@ __device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int
   }
   if (b.span <= 0) return;
   // gradient: ordered pairs of types (one structure); its tables hold one window
-  const bool on = b.route[0] && b.nbins[0] <= kBinCap;
+  const bool on = route0 && nbins0 <= kBinCap;
   int64_t units = 0;
-  for (int x0 = 0; x0 < b.T * b.T; x0 += 256) {
+  for (int x0 = 0; x0 < b.T * b.T; x0 += blockDim.x) {
     const int x = x0 + threadIdx.x;
     GradEntry en{};
     int64_t count = 0;
@@ -154,7 +162,7 @@ __device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int
       count = on ? static_cast<int64_t>((en.na + kWave - 1) / kWave) * en.chunks : 0;
     }
     int64_t sum = 0;
-    const int64_t incl = scan256(count, &sum);
+    const int64_t incl = scan_block(count, &sum);
     if (x < b.T * b.T) {
       en.unit0 = units + incl - count;
       b.gents[x] = en;
@@ -169,6 +177,53 @@ __device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int
   }
 }
 
+// Planning by one work-group (256 or 1024 threads), after b.nbins (bins per
+// structure, 0: too many) and the type segments toff are known.
+__device__ inline void bins_plan(const BinArgs& b, const DescView& sd, const int32_t* toff) {
+  __shared__ int32_t fallback;
+  if (threadIdx.x == 0) fallback = 0;
+  const int64_t ndone = static_cast<int64_t>(b.S) * ((b.Nq + kWave - 1) / kWave);
+  for (int64_t k = threadIdx.x; k < ndone; k += blockDim.x) b.done[k] = 0;
+  __syncthreads();
+  int64_t pool = 0;
+  for (int s0 = 0; s0 < b.S; s0 += blockDim.x) {
+    const int s = s0 + threadIdx.x;
+    const int32_t nb = s < b.S ? b.nbins[s] : 0;
+    const int64_t want = static_cast<int64_t>(nb) * b.TP;
+    int64_t sum = 0;
+    const int64_t incl = scan_block(want, &sum);
+    if (s < b.S) {
+      const int64_t off = pool + incl - want;
+      const bool ok = nb > 0 && off + want <= b.pool_cap;
+      b.pool_off[s] = ok ? off : 0;
+      b.route[s] = ok ? 1 : 0;
+      if (!ok) atomicAdd(&fallback, 1);
+    }
+    pool += sum;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    b.meta->pool_used = pool < b.pool_cap ? pool : b.pool_cap;
+    b.meta->fallback = fallback;
+  }
+  plan_items(b, toff, b.nbins[0], b.pool_off[0], b.route[0]);
+}
+
+// The same for a single structure, of nbins bins (0: too many).
+__device__ inline void bins_plan_one(const BinArgs& b, int32_t nbins, const int32_t* toff) {
+  const int64_t want = static_cast<int64_t>(nbins) * b.TP;
+  const int32_t ok = nbins > 0 && want <= b.pool_cap ? 1 : 0;
+  for (int64_t k = threadIdx.x; k < (b.Nq + kWave - 1) / kWave; k += blockDim.x) b.done[k] = 0;
+  if (threadIdx.x == 0) {
+    b.nbins[0] = nbins;
+    b.pool_off[0] = 0;
+    b.route[0] = ok;
+    b.meta->pool_used = ok ? want : 0;
+    b.meta->fallback = ok ? 0 : 1;
+  }
+  plan_items(b, toff, nbins, 0, ok);
+}
+
 // Bin b spans [b, b + 1) of sqrt(t^2 + 1/4), so t^2 + 1/4 has its centre at
 // b^2 + b + 1/2 and half width b + 1/2 there; the first bin begins at 1/4, t = 0.
 // The radius (in units of 1 / invh) of the node at v in [-1, 1] over the bin:
@@ -177,13 +232,17 @@ __device__ __forceinline__ double bin_node_radius(int bin, double v) {
   return sqrt(bin == 0 ? 0.375 + 0.375 * v : static_cast<double>(bin) * bin + bin + 0.25 + c * v);
 }
 
-// v over the bin from a pair's u = (t^2 + 1/4 - (b + 1/2)^2) / (b + 1/2):
-// v = scale (u + offset).
+// v over the bin from a pair's u = (t^2 + 1/4 - (b + 1/2)^2) rc:
+// v = scale (u + offset).  rc is the pair kernels' own reciprocal of b + 1/2,
+// rounded as there: its error, the same for every pair of a bin, would not
+// average out (6,000 atoms: 8e-8 of I at its minima).
 struct BinShift {
   double scale, offset;
 };
 __device__ __forceinline__ BinShift bin_shift(int bin) {
-  return bin == 0 ? BinShift{4.0 / 3.0, -0.75} : BinShift{1.0, -0.25 / (bin + 0.5)};
+  const float tc = static_cast<float>(bin) + 0.5f;
+  const double rc = static_cast<double>(__builtin_amdgcn_rcpf(tc));
+  return bin == 0 ? BinShift{4.0 / 3.0, -0.75} : BinShift{1.0 / (rc * static_cast<double>(tc)), -0.25 * rc};
 }
 
 // Weights of a bin's six nodes from its integer sums: the sums of u^k, moved to
@@ -196,6 +255,7 @@ __device__ __forceinline__ void bin_node_weights(const unsigned long long (&p)[k
 #pragma unroll
   for (int k = 0; k < kBinMoments; ++k)
     m[k] = static_cast<double>(static_cast<long long>(p[k])) / static_cast<double>(1ll << kBits[k]);
+  m[4] = fma(-kBinBias4, m[0], m[4]);
   const BinShift sh = bin_shift(bin);
   const double al = sh.offset;
   // sums of (u + al)^k by repeated Horner shifts: m_k += al m_{k-1}, from the top

@@ -147,6 +147,7 @@ __global__ __launch_bounds__(256) void k_pack_scan(DescView sd, int32_t T, int32
   for (int64_t k = threadIdx.x; k < nb * T; k += blockDim.x) base[k] += tot[k % T];
   if (!bins.on) return;
   __shared__ float ext[4][6];
+  __shared__ int32_t nbins_s;
   float e[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
   for (int64_t k = threadIdx.x; k < nb; k += blockDim.x) {
     const float* p = bins.bbox + (d.pack_off + k) * 6;
@@ -167,18 +168,17 @@ __global__ __launch_bounds__(256) void k_pack_scan(DescView sd, int32_t T, int32
     for (int c = 0; c < 6; ++c) ext[w][c] = e[c];
   __syncthreads();
   if (threadIdx.x == 0) {
-    double sq = 0.0;
+    float lo[3], hi[3];
     for (int c = 0; c < 3; ++c) {
-      const float lo = fminf(fminf(ext[0][c], ext[1][c]), fminf(ext[2][c], ext[3][c]));
-      const float hi = fmaxf(fmaxf(ext[0][c + 3], ext[1][c + 3]), fmaxf(ext[2][c + 3], ext[3][c + 3]));
-      const double x = d.n > 0 ? static_cast<double>(hi) - static_cast<double>(lo) : 0.0;
-      sq = fma(x, x, sq);
-      bins.centre[3 * static_cast<int64_t>(s) + c] = d.n > 0 ? 0.5 * (static_cast<double>(hi) + static_cast<double>(lo)) : 0.0;
+      lo[c] = fminf(fminf(ext[0][c], ext[1][c]), fminf(ext[2][c], ext[3][c]));
+      hi[c] = fmaxf(fmaxf(ext[0][c + 3], ext[1][c + 3]), fmaxf(ext[2][c + 3], ext[3][c + 3]));
     }
-    bins.nbins[s] = bin_count(bins, sqrt(sq), d.n);
+    const int32_t nbins = bin_bounds(bins, s, d.n, lo, hi);
+    bins.nbins[s] = nbins;
+    nbins_s = nbins;
   }
   __syncthreads();
-  if (bins.S == 1) bins_plan(bins, sd, toff);
+  if (bins.S == 1) bins_plan_one(bins, nbins_s, toff);
 }
 
 __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __restrict__ coords,
@@ -209,18 +209,126 @@ __global__ __launch_bounds__(kPackBlock) void k_pack_scatter(const float* __rest
   xyz[dest] = make_double4(x, y, z, 0.0);
   if (bins.on) {
     const int32_t* o = bins.toff + static_cast<int64_t>(s) * (T + 1) + t;
-    const double* c = bins.centre + 3 * static_cast<int64_t>(s);
-    const double px = (x - c[0]) * bins.invh, py = (y - c[1]) * bins.invh, pz = (z - c[2]) * bins.invh;
-    const int64_t at = o[0] + bin_spread(static_cast<int32_t>(dest - o[0]), o[1] - o[0]);
-    if (bins.span > 0) bins.order[at] = static_cast<int32_t>(src);
-    double* to = bins.xs + at;
-    to[0] = px;
-    to[bins.ld] = py;
-    to[2 * bins.ld] = pz;
-    to[3 * bins.ld] = fma(pz, pz, fma(py, py, px * px));
+    bin_store(bins, s, o[0], o[1], static_cast<int32_t>(dest - o[0]), static_cast<int32_t>(src), x, y, z);
   }
   tsort[dest] = t;
   perm[dest] = static_cast<int32_t>(src);
+}
+
+// The whole pack of one small structure by one work-group: the same stable
+// order, and the binned form's bounds, plan and cleared sums.  Three kernels
+// of a few microseconds each cost such a call more than their work.
+__global__ __launch_bounds__(kSmallThreads) void k_pack_small(const float* __restrict__ coords,
+                                                              const int32_t* __restrict__ types, DescView sd,
+                                                              int32_t T, int32_t* __restrict__ toff,
+                                                              double4* __restrict__ xyz, int32_t* __restrict__ tsort,
+                                                              int32_t* __restrict__ perm,
+                                                              const float* __restrict__ table, int32_t Nq, int32_t ldt,
+                                                              float* __restrict__ tabp,
+                                                              unsigned long long* __restrict__ counter, BinArgs bins) {
+  constexpr int kRounds = kSmallAtoms / kSmallThreads, kWaves = kSmallThreads / kWave;
+  static_assert(kRounds * kWaves <= kWave, "a wave scans one type's counts over all chunks of 64 atoms");
+  __shared__ int32_t cnt[kRounds * kWaves][kSmallTypes];  // [chunk of 64 atoms][type]: count, then first row within the type
+  __shared__ int32_t start[kSmallTypes + 1];
+  __shared__ float ext[kWaves][6];
+  __shared__ int32_t nbins_s;
+  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+  const StructDesc d = sd.one;
+  const int n = d.n;
+  int ty[kRounds], rank[kRounds];
+  float x[kRounds], y[kRounds], z[kRounds];
+  float e[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int a = r * kSmallThreads + tid;
+    const bool live = a < n;
+    ty[r] = live ? clamp_type(types[a], T) : -1;
+    x[r] = live ? coords[3 * a] : 0.f;
+    y[r] = live ? coords[3 * a + 1] : 0.f;
+    z[r] = live ? coords[3 * a + 2] : 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    rank[r] = 0;
+    for (int t = 0; t < T; ++t) {  // (also where no atoms are left: the counts are zero)
+      const unsigned long long same = __ballot(ty[r] == t);
+      if (ty[r] == t) rank[r] = __popcll(same & ((1ull << lane) - 1));
+      if (lane == 0) cnt[r * kWaves + w][t] = __popcll(same);
+    }
+    if (ty[r] >= 0) {
+      const float c[3] = {x[r], y[r], z[r]};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const bool bad = !isfinite(c[k]);
+        e[k] = fminf(e[k], bad ? -INFINITY : c[k]);
+        e[3 + k] = fmaxf(e[3 + k], bad ? INFINITY : c[k]);
+      }
+    }
+  }
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      e[k] = fminf(e[k], __shfl_xor(e[k], off, kWave));
+      e[3 + k] = fmaxf(e[3 + k], __shfl_xor(e[3 + k], off, kWave));
+    }
+  }
+  if (lane == 0)
+    for (int k = 0; k < 6; ++k) ext[w][k] = e[k];
+  __syncthreads();
+  for (int t = w; t < T; t += kWaves) {
+    const int32_t c = lane < kRounds * kWaves ? cnt[lane][t] : 0;
+    int32_t v = c;
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int32_t u = __shfl_up(v, off, kWave);
+      if (lane >= off) v += u;
+    }
+    if (lane < kRounds * kWaves) cnt[lane][t] = v - c;
+    if (lane == kWave - 1) start[t + 1] = v;
+  }
+  __syncthreads();
+  if (w == 0) {
+    // (types' starts by lane 0; the waves' boxes by the lanes)
+    if (lane == 0) {
+      int32_t run = 0;
+      start[0] = 0;
+      for (int t = 0; t < T; ++t) start[t + 1] = run += start[t + 1];
+    }
+    if (bins.on) {
+      float lo[3], hi[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = ext[lane % kWaves][k];
+        hi[k] = ext[lane % kWaves][3 + k];
+      }
+      for (int off = kWaves / 2; off > 0; off >>= 1) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          lo[k] = fminf(lo[k], __shfl_xor(lo[k], off, kWave));
+          hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off, kWave));
+        }
+      }
+      if (lane == 0) nbins_s = bin_bounds(bins, 0, n, lo, hi);
+    }
+  }
+  __syncthreads();
+  for (int t = tid; t <= T; t += kSmallThreads) toff[t] = start[t];
+  pad_table(table, T, Nq, ldt, tabp, counter, tid, kSmallThreads);
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int a = r * kSmallThreads + tid, t = ty[r];
+    if (t < 0) continue;
+    const int32_t row = cnt[a / kWave][t] + rank[r], dest = start[t] + row;
+    xyz[dest] = make_double4(x[r], y[r], z[r], 0.0);
+    tsort[dest] = t;
+    perm[dest] = a;
+    if (bins.on) bin_store(bins, 0, start[t], start[t + 1], row, a, x[r], y[r], z[r]);
+  }
+  if (!bins.on) return;
+  bins_plan_one(bins, nbins_s, start);
+  const int64_t want = static_cast<int64_t>(nbins_s) * bins.TP;
+  if (!bins.pool || want > bins.pool_cap) return;
+  const int64_t words = want * kBinMoments;
+  for (int64_t k = tid; k < words; k += kSmallThreads) bins.pool[k] = 0;
 }
 
 // Copy the caller's [T][Nq] table into [T][ldt] with zeros in columns >= Nq.
@@ -273,6 +381,11 @@ hipError_t launch_pack(const float* coords, const int32_t* types, const DescView
                        int32_t* tsort, int32_t* perm, const float* table, int32_t Nq, int32_t ldt, float* tabp,
                        unsigned long long* counter, const BinArgs* bins, hipStream_t st) {
   const BinArgs b = bins ? *bins : BinArgs{};
+  if (small_pack(sd, S, T, ldt)) {
+    hipLaunchKernelGGL(k_pack_small, dim3(1), dim3(kSmallThreads), 0, st, coords, types, sd, T, toff, xyz, tsort, perm,
+                       table, Nq, ldt, tabp, counter, b);
+    return hipGetLastError();
+  }
   // the counting kernel pads the table on the side, unless it has too few
   // threads for its size
   const bool pad = n_pack_blocks > 0 && static_cast<int64_t>(T) * ldt <= 16 * kPackBlock * n_pack_blocks;
@@ -371,64 +484,10 @@ __global__ __launch_bounds__(256) void k_reduce_final(DescView sd, const double*
                                                       const double* __restrict__ asum,
                                                       const float* __restrict__ table, int32_t T, int32_t Nq,
                                                       double q0, double dq, const double* __restrict__ qdev,
-                                                      BinArgs b, double* __restrict__ I_out) {
-  __shared__ double part[4][kWave];
-  const int s = blockIdx.x;
-  const StructDesc d = sd.get(s);
-  const int32_t* o = toff ? toff + static_cast<int64_t>(s) * (T + 1) : nullptr;
-  const int64_t nb = ceil_div(d.n, kPackBlock);
-  // a binned structure's pair sums are complete (no 2/q factor)
-  const bool binned = b.on && b.route[s];
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+                                                      double* __restrict__ I_out) {
   const int groups = static_cast<int>(ceil_div(Nq, kWave));
-  for (int g = blockIdx.y; g < groups; g += gridDim.y) {  // (grid.y is capped at 65535)
-    const int m = g * kWave + lane;
-    const bool vm = m < Nq;
-    const double qm = vm ? (qdev ? qdev[m] : q0 + m * dq) : 1.0;
-    // the strip pair sums: wave w takes slices w, w + 4, ... in order
-    double pairs = 0.0;
-    if (vm && qm != 0.0) {
-      if (binned) {
-        // (in order, by the first wave: one work-group that adds its own rows
-        // gives the same sum)
-        const int rows = w == 0 ? bin_rows(b, b.nbins[s]) : 0;
-        const double* p = b.part + static_cast<int64_t>(s) * b.rows * Nq + m;
-#pragma unroll 16
-        for (int k = 0; k < rows; ++k) pairs += p[static_cast<int64_t>(k) * Nq];
-      } else {
-        for (int64_t k = w; k < d.n_slices; k += 4) pairs += slice_sums[(d.slice_off + k) * Nq + m];
-      }
-    }
-    __syncthreads();
-    part[w][lane] = pairs;
-    __syncthreads();
-    if (w == 0 && vm) {
-      double val;
-      if (qm == 0.0) {
-        double f = 0.0;
-        if (asum) {
-          for (int64_t k = 0; k < nb; ++k) f += asum[((d.pack_off + k) * 2 + 0) * Nq + m];
-        } else {
-          for (int t = 0; t < T; ++t)
-            f += static_cast<double>(o[t + 1] - o[t]) * static_cast<double>(table[static_cast<int64_t>(t) * Nq + m]);
-        }
-        val = f * f;
-      } else {
-        const double psum = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-        double diag = 0.0;
-        if (asum) {
-          for (int64_t k = 0; k < nb; ++k) diag += asum[((d.pack_off + k) * 2 + 1) * Nq + m];
-        } else {
-          for (int t = 0; t < T; ++t) {
-            const double f = table[static_cast<int64_t>(t) * Nq + m];
-            diag += static_cast<double>(o[t + 1] - o[t]) * f * f;
-          }
-        }
-        val = binned ? diag + psum : diag + (2.0 / qm) * psum;
-      }
-      I_out[static_cast<int64_t>(d.orig) * Nq + m] = val;
-    }
-  }
+  for (int g = blockIdx.y; g < groups; g += gridDim.y)  // (grid.y is capped at 65535)
+    reduce_final(sd, blockIdx.x, g, slice_sums, toff, asum, table, T, Nq, q0, dq, qdev, I_out);
 }
 
 hipError_t launch_reduce_slices(const DescView& sd, int64_t n_slices_total, const double* partial, int32_t row,
@@ -436,17 +495,6 @@ hipError_t launch_reduce_slices(const DescView& sd, int64_t n_slices_total, cons
   if (n_slices_total > 0) {
     const dim3 grid(static_cast<uint32_t>(n_slices_total), static_cast<uint32_t>(std::min<int64_t>(ceil_div(row, kWave), 65535)));
     hipLaunchKernelGGL(k_reduce_slices, grid, dim3(256), 0, st, sd, partial, row, slice_sums, fallback);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_final(const DescView& sd, int32_t S, const double* slice_sums, const int32_t* toff,
-                               const double* asum, const float* table, int32_t T, int32_t Nq, double q0, double dq,
-                               const double* qdev, const BinArgs* bins, double* I_out, hipStream_t st) {
-  const uint32_t qgroups = static_cast<uint32_t>(std::min<int64_t>(ceil_div(Nq, kWave), 65535));
-  if (S > 0) {
-    hipLaunchKernelGGL(k_reduce_final, dim3(S, qgroups), dim3(256), 0, st, sd, slice_sums, toff, asum, table, T, Nq,
-                       q0, dq, qdev, bins ? *bins : BinArgs{}, I_out);
   }
   return hipGetLastError();
 }
@@ -459,7 +507,11 @@ hipError_t launch_reduce(const DescView& sd, int32_t S, int64_t n_slices_total, 
     hipLaunchKernelGGL(k_reduce_slices, dim3(static_cast<uint32_t>(n_slices_total), qgroups), dim3(256), 0, st, sd,
                        partial, Nq, slice_sums, nullptr);
   }
-  return launch_reduce_final(sd, S, slice_sums, toff, asum, table, T, Nq, q0, dq, qdev, nullptr, I_out, st);
+  if (S > 0) {
+    hipLaunchKernelGGL(k_reduce_final, dim3(S, qgroups), dim3(256), 0, st, sd, slice_sums, toff, asum, table, T, Nq,
+                       q0, dq, qdev, I_out);
+  }
+  return hipGetLastError();
 }
 
 }  // namespace sas

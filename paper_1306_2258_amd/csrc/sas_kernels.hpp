@@ -94,6 +94,17 @@ struct AdjArgs {
   const int32_t* binned; // non-null: 1 when the binned form does the work
 };
 
+// One structure packed by one work-group (three kernels otherwise): small
+// enough that its few rounds of 1024 atoms, and the table's, stay short (whole
+// calls at 2,000 atoms: 40 us against 43; at 4,000: 58 against 51).
+constexpr int kSmallAtoms = 2048, kSmallTypes = 16, kSmallThreads = 1024;
+inline bool small_pack(int64_t n, int32_t S, int32_t T, int32_t ldt) {
+  return S == 1 && n > 0 && n <= kSmallAtoms && T <= kSmallTypes && static_cast<int64_t>(T) * ldt <= 16384;
+}
+inline bool small_pack(const DescView& sd, int32_t S, int32_t T, int32_t ldt) {
+  return S == 1 && small_pack(sd.one.n, S, T, ldt);
+}
+
 struct BinArgs;  // the binned form (sas_bins.hpp)
 
 // Host-side helpers implemented in sas_kernels.hip / sas_adjoint.hip.
@@ -116,12 +127,6 @@ hipError_t launch_forward(const ForwardArgs& a, int64_t n_strips_total, int32_t 
 hipError_t launch_reduce(const DescView& sd, int32_t S, int64_t n_slices_total, const double* partial,
                          double* slice_sums, const int32_t* toff, const double* asum, const float* table, int32_t T,
                          int32_t Nq, double q0, double dq, const double* qdev, double* I_out, hipStream_t st);
-
-// The second level alone; with `bins`, a binned structure's pair sums come from
-// its partial profiles there.
-hipError_t launch_reduce_final(const DescView& sd, int32_t S, const double* slice_sums, const int32_t* toff,
-                               const double* asum, const float* table, int32_t T, int32_t Nq, double q0, double dq,
-                               const double* qdev, const BinArgs* bins, double* I_out, hipStream_t st);
 
 // Sum rows of `row` values over each slice of kSliceTiles strips, in order
 // (nothing when *fallback is given and 0).
