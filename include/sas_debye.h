@@ -261,10 +261,12 @@ sas_status sas_debye_grad_table(sas_ctx* ctx, const float* coords, const int32_t
  * Orientation-averaged and hybrid profiles (approximate at a stated
  * tolerance).  Eq. 1 averages |A(q,u)|^2, A = sum_j f_j exp(i q u.r_j), over
  * directions u; a product rule with L+1 Gauss-Legendre nodes in cos(theta)
- * and 2L+1 uniform nodes in phi averages it to relative accuracy about tol
- * when L >= q R + O((q R)^(1/3)) (R: largest distance from the centre), at
+ * and 2L+1 or more uniform nodes in phi averages it to relative accuracy about
+ * tol when L >= q R + O((q R)^(1/3)) (R: largest distance from the centre), at
  * a cost of (L+1)(2L+1) N per q against N^2/2 for the direct sum: cheaper
- * at low q, as the Background section argues (O(q^2 D^2) directions).
+ * at low q, as the Background section argues (O(q^2 D^2) directions).  Only
+ * the directions of one half of the sphere are evaluated (A(q,-u) is the
+ * conjugate of A(q,u)); the split below keeps the cost named here.
  *
  * sas_orient_degree: the L used for q, R and tol (host only; -1 for invalid
  * arguments).

