@@ -2,14 +2,23 @@
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--no-extras]
 
-A step is one full profile evaluation (pack -> pair kernel -> FP64 reduce)
+A step is one full profile evaluation (pack -> pair kernel -> FP64 sums)
 of the 50,000-atom double-helix rod on a 200-point q grid over [0, 1] 1/A,
 with inputs already resident in HBM.  The headline value is the whole-job
 pair.q rate: N(N-1)/2 pairs times the 199 q values with q > 0, per second.
+Every pair's distance is formed and every q receives every pair; the binned
+form's pair kernel visits a pair once (not once per q), so the rate counts the
+job's pairs and q, not sines evaluated.
 
 The JSON line also carries
-  roofline      the pair kernel's FP32 rate from HIP events recorded on its own
-                launch stream: the flops its recurrence performs per pair.q
+  roofline      the pair kernel's rate from HIP events recorded on its own
+                launch stream.  Binned form: its three 64-bit LDS additions per
+                pair against the rate of conflict-free ones (a wave instruction
+                every 4 cycles per CU), and the VALU instructions beside them
+                from stored counters, which the additions add to.  Recurrence:
+                as in the leg below;
+  recurrence    the same profile by the recurrence over q (a forced tile
+                shape): the flops it performs per pair.q
                 (4.5: one FMA and one add to step sin(q r), an add or FMA to
                 accumulate) against the MI355X FP32 vector peak (157.3
                 TFLOP/s, one wave64 FMA per SIMD every 2 cycles at 2.4 GHz);
@@ -55,17 +64,20 @@ NOMINAL_FLOPS_PER_PAIR_Q_ADJ = 12.0
 ISSUE_CEILING_PAIR_Q = SIMDS * CLOCK_HZ * 64 / (INSTR_PER_PAIR_Q * PEAK_CYCLES_PER_WAVE_INSTR)
 MIX_CYCLES_PER_WAVE_INSTR = 2.3
 MIX_CEILING_PAIR_Q = SIMDS * CLOCK_HZ * 64 / (INSTR_PER_PAIR_Q * MIX_CYCLES_PER_WAVE_INSTR)
+# The binned form: 64-bit LDS additions per pair, and the rate of conflict-free
+# ones (a microbenchmark on MI355X: 4.0 cycles per wave instruction and CU; 11.7
+# where the 64 lanes' banks are random).
+LDS_ADDS_PER_PAIR = 3
+LDS_ADD_PEAK = 256 * CLOCK_HZ * 64 / 4.0
 BASE_SEED_PER_ATOM = 13062258 + 50
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_forward_dna_rod_50k_traffic.txt")
-VALU_FILE = os.path.join(ROOT, "profiles", "k_forward_dna_rod_50k_valu.txt")
-# What the headline pair kernel's code depends on: its template and device
-# helpers, and the argument structs and wave size from the internal header
-# (the rest of that header and of the .hip files declares or defines other
-# kernels, which do not change this one).
+COUNTER_FILE = os.path.join(ROOT, "profiles", "k_bins_dna_rod_50k_counters.txt")
+# What the headline pair kernel's code depends on: the binned form's sources,
+# and the wave size from the internal header (the rest of that header declares
+# other kernels, which do not change this one).
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1306_2258_amd", "csrc", f)
-                  for f in ("sas_forward_kernel.hpp", "sas_forward.hpp", "sas_device.hpp", "sas_schedule.hpp")]
+                  for f in ("sas_bins.hip", "sas_bins.hpp", "sas_bins_device.hpp")]
 KERNEL_HEADER = os.path.join(ROOT, "paper_1306_2258_amd", "csrc", "sas_kernels.hpp")
-KERNEL_HEADER_PARTS = ("kWave", "StructDesc", "DescView", "Geometry", "ForwardArgs")
+KERNEL_HEADER_PARTS = ("kWave",)
 
 
 def _code_only(text: str) -> str:
@@ -112,42 +124,34 @@ def stored_counters(path: str, kernel_name: str):
     return kv
 
 
-def stored_traffic(kernel_name: str):
-    """HBM bytes per pair-kernel launch from the committed FETCH/WRITE summary."""
-    kv = stored_counters(TRAFFIC_FILE, kernel_name)
-    try:
-        return float(kv["hbm_bytes_per_launch"]) if kv else None
-    except (KeyError, ValueError):
-        return None
-
-
-def stored_valu(kernel_name: str, work: float, kern_ms: float):
-    """Executed FP32 rate and VALU issue figures from the committed VALU
-    counter summary, scaled to this run's measured kernel time."""
-    kv = stored_counters(VALU_FILE, kernel_name)
-    if not kv:
-        return None
-    try:
-        flops = float(kv["SQ_INSTS_VALU_FLOPS_FP32"]) * 64.0
+def bins_roofline(n: int, kern_ms: float):
+    """The binned pair kernel: LDS additions against their peak, and from the
+    committed counters its VALU instructions and HBM bytes, scaled to this
+    run's kernel time."""
+    pairs = n * (n - 1) / 2.0
+    rate = LDS_ADDS_PER_PAIR * pairs / (kern_ms / 1e3)
+    out = {"bound": "lds", "achieved": rate, "peak": LDS_ADD_PEAK, "unit": "64-bit LDS additions/s",
+           "frac": rate / LDS_ADD_PEAK, "traffic": None, "kernel": "k_bins", "kernel_ms": kern_ms,
+           "pairs_per_s": pairs / (kern_ms / 1e3), "lds_adds_per_pair": LDS_ADDS_PER_PAIR}
+    kv = stored_counters(COUNTER_FILE, "k_bins")
+    if kv:
         insts = float(kv["SQ_INSTS_VALU"])
-    except (KeyError, ValueError):
-        return None
-    tflops = flops / (kern_ms / 1e3) / 1e12
-    out = {"executed_fp32_flops_per_pair_q": flops / work, "executed_fp32_tflops": tflops,
-           "frac_of_fp32_peak": tflops / PEAK_FP32_TFLOPS, "valu_insts_per_pair_q": insts * 64.0 / work,
-           "cycles_per_valu_inst_per_simd": (kern_ms / 1e3) * 2.4e9 / (insts / 1024.0),
-           "source": os.path.relpath(VALU_FILE, ROOT)}
-    # GRBM_GUI_ACTIVE counts busy cycles of each of the 8 XCDs: over the
-    # kernel's time it gives the clock the chip actually ran at, and the peak
-    # scaled to that clock
-    try:
-        ghz = float(kv["GRBM_GUI_ACTIVE"]) / 8.0 / (kern_ms / 1e3) / 1e9
-    except (KeyError, ValueError):
-        ghz = None
-    if ghz:
-        out["effective_clock_ghz"] = ghz
-        out["peak_fp32_tflops_at_clock"] = PEAK_FP32_TFLOPS * ghz / 2.4
+        out["traffic"] = float(kv["hbm_bytes_per_launch"])
+        out["valu_insts_per_pair"] = insts * 64.0 / pairs
+        out["cycles_per_valu_inst_per_simd"] = (kern_ms / 1e3) * CLOCK_HZ / (insts / SIMDS)
+        out["counters"] = os.path.relpath(COUNTER_FILE, ROOT)
     return out
+
+
+def recurrence_roofline(work: float, kern_ms: float, kernel: str):
+    achieved = EXEC_FLOPS_PER_PAIR_Q * work / (kern_ms / 1e3) / 1e12
+    return {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
+            "frac": achieved / PEAK_FP32_TFLOPS, "kernel": kernel, "kernel_ms": kern_ms,
+            "flops_per_pair_q": EXEC_FLOPS_PER_PAIR_Q,
+            "frac_nominal": NOMINAL_FLOPS_PER_PAIR_Q * work / (kern_ms / 1e3) / 1e12 / PEAK_FP32_TFLOPS,
+            "nominal_flops_per_pair_q": NOMINAL_FLOPS_PER_PAIR_Q,
+            "issue_frac": (work / (kern_ms / 1e3)) / ISSUE_CEILING_PAIR_Q,
+            "issue_frac_mix_floor": (work / (kern_ms / 1e3)) / MIX_CEILING_PAIR_Q}
 
 
 def log(msg):
@@ -233,10 +237,13 @@ def main(argv=None):
     work = pair_q(m.n, m.q)
     value = work / (ms_step / 1e3)
     kern_ms = kt["forward_ms"] / max(kt["forward_launches"], 1)
-    achieved = EXEC_FLOPS_PER_PAIR_Q * work / (kern_ms / 1e3) / 1e12
     bj, qc = ctx.variant()
     launch = ctx.launch()
-    kname = f"k_forward_persist<{qc}, {bj}>" if launch == "persistent" else f"k_forward<{qc}, {bj}>"
+    binned = (bj, qc) == (0, 0)
+    if binned:
+        roofline = bins_roofline(m.n, kern_ms)
+    else:
+        roofline = recurrence_roofline(work, kern_ms, pair_kernel_name(bj, qc, launch))
     if args.copy_probe > 0:
         nbytes = int(args.copy_probe)
         src = torch.empty(nbytes // 4, dtype=torch.float32, device=dev).fill_(1.0)
@@ -262,21 +269,12 @@ def main(argv=None):
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": "dna_rod_50k", "atoms": m.n, "nq": len(m.q), "q_range": [0.0, 1.0], "types": 5,
-                   "pair_q_per_step": work, "variant": {"bj": bj, "qc": qc, "launch": launch}},
+                   "pair_q_per_step": work, "form": "binned" if binned else "recurrence",
+                   "variant": {"bj": bj, "qc": qc, "launch": launch}},
         "ms_per_step_median": float(np.median(per_step)) if per_step else None,
         "ms_per_step_min": float(np.min(per_step)) if per_step else None,
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_FP32_TFLOPS, "traffic": stored_traffic(kname),
-                     "kernel": kname, "kernel_ms": kern_ms, "flops_per_pair_q": EXEC_FLOPS_PER_PAIR_Q,
-                     "frac_nominal": NOMINAL_FLOPS_PER_PAIR_Q * work / (kern_ms / 1e3) / 1e12 / PEAK_FP32_TFLOPS,
-                     "nominal_flops_per_pair_q": NOMINAL_FLOPS_PER_PAIR_Q,
-                     "issue_frac": (work / (kern_ms / 1e3)) / ISSUE_CEILING_PAIR_Q,
-                     "issue_frac_mix_floor": (work / (kern_ms / 1e3)) / MIX_CEILING_PAIR_Q,
-                     "valu_counters": stored_valu(kname, work, kern_ms)},
+        "roofline": roofline,
     }
-    vc = result["roofline"]["valu_counters"]
-    if vc and vc.get("peak_fp32_tflops_at_clock"):
-        result["roofline"]["frac_clock_adjusted"] = achieved / vc["peak_fp32_tflops_at_clock"]
 
     # accuracy of the timed output against the stored FP64 oracle profile
     gold = os.path.join(ROOT, "tests", "golden", "dna_rod_50k.txt")
@@ -315,7 +313,11 @@ def main(argv=None):
         except Exception as exc:
             result["grad"] = {"error": str(exc)[:200]}
         try:
-            result["direct"] = bench_direct(sd, W, torch, dev, ms_step)
+            result["recurrence"] = bench_recurrence(sd, torch, coords, types, table, m, out)
+        except Exception as exc:
+            result["recurrence"] = {"error": str(exc)[:200]}
+        try:
+            result["direct"] = bench_direct(sd, W, torch, dev, result["recurrence"].get("ms", ms_step))
         except Exception as exc:
             result["direct"] = {"error": str(exc)[:200]}
         try:
@@ -353,6 +355,30 @@ def _time(fn, torch, reps=3):
     return e0.elapsed_time(e1) / reps
 
 
+def pair_kernel_name(bj: int, qc: int, launch: str) -> str:
+    return f"k_forward_persist<{qc}, {bj}>" if launch == "persistent" else f"k_forward<{qc}, {bj}>"
+
+
+def bench_recurrence(sd, torch, coords, types, table, m, binned):
+    """The headline profile by the recurrence over q (a forced tile shape), and
+    the largest relative difference between the two forms."""
+    ctx = sd.Context(0)
+    ctx.set_variant(256, 200)
+    I = sd.debye_profile(coords, types, table, m.q, ctx=ctx)
+    diff = float(((I - binned).abs() / I.abs()).max())
+    ctx.read_timing()
+    ctx.enable_timing(True)
+    ms = _time(lambda: sd.debye_profile(coords, types, table, m.q, ctx=ctx), torch)
+    ctx.enable_timing(False)
+    kt = ctx.read_timing()
+    bj, qc = ctx.variant()
+    work = pair_q(m.n, m.q)
+    log(f"recurrence {ms:.3f} ms, max rel diff to the headline {diff:.2e}")
+    return {"ms": ms, "pair_q_per_s": work / (ms / 1e3), "max_rel_diff": diff,
+            "roofline": recurrence_roofline(work, kt["forward_ms"] / max(kt["forward_launches"], 1),
+                                            pair_kernel_name(bj, qc, ctx.launch()))}
+
+
 def bench_batched(sd, W, torch, dev):
     """256 globular structures (500..8000 atoms) on a 100-point grid: one
     batched evaluation (plan replay) against 256 plain calls."""
@@ -372,11 +398,11 @@ def bench_batched(sd, W, torch, dev):
         bj, qc = ctx.variant()
         res["plan_variant"] = {"bj": bj, "qc": qc, "launch": ctx.launch()}
         plan.close()
-        # the tuned shape with each launch of the pair kernel forced
+        # the recurrence with each launch of its pair kernel forced
         ab = {}
         for launch in ("grid", "persistent"):
             actx = sd.Context(0)
-            actx.set_variant(bj, qc)
+            actx.set_variant(128, 100)
             actx.set_form(launch)
             p2 = sd.BatchedPlan(coords, types, e.offsets, table, e.q, ctx=actx)
             ab[f"ms_{launch}"] = _time(p2.execute, torch)
@@ -407,9 +433,9 @@ def bench_batched(sd, W, torch, dev):
 
 
 def bench_direct(sd, W, torch, dev, ms_recurrence):
-    """The direct form (one sine per pair and q) on the 50,000-atom rod:
-    a 200-point log-spaced grid on [1e-3, 1], and the benchmark's uniform
-    grid forced into the direct form (what the recurrence saves)."""
+    """The 50,000-atom rod on a 200-point log-spaced grid on [1e-3, 1], and the
+    benchmark's uniform grid forced into the direct form (one sine per pair and
+    q; what the recurrence saves)."""
     res = {}
     for label, m, form in (("log_grid_200", W.dna_rod_50k(q=W.log_grid(1e-3, 1.0, 200)), "auto"),
                            ("uniform_grid_200_forced", W.dna_rod_50k(), "direct")):
@@ -427,9 +453,9 @@ def bench_direct(sd, W, torch, dev, ms_recurrence):
         kt = ctx.read_timing()
         kern_ms = kt["forward_ms"] / max(kt["forward_launches"], 1)
         work = pair_q(m.n, m.q)
-        res[label] = {"form": ctx.form(), "ms": ms, "kernel_ms": kern_ms, "pair_q_per_s": work / (ms / 1e3),
+        res[label] = {"form": ctx.form(), "binned": ctx.variant() == (0, 0), "ms": ms, "kernel_ms": kern_ms, "pair_q_per_s": work / (ms / 1e3),
                       "kernel_pair_q_per_s": work / (kern_ms / 1e3)}
-        log(f"direct form {label}: {ms:.3f} ms (pair kernel {kern_ms:.3f} ms)")
+        log(f"{label}: {ms:.3f} ms (pair kernel {kern_ms:.3f} ms)")
     res["recurrence_speedup"] = res["uniform_grid_200_forced"]["ms"] / ms_recurrence
     return res
 
@@ -585,14 +611,18 @@ def bench_grad(sd, W, torch, dev):
     res = {"atoms": m.n, "nq": len(m.q), "ms_forward": ms_fwd, "ms_forward_plus_adjoint": ms_grad,
            "adjoint_kernel_ms": adj_ms, "ratio": ms_grad / ms_fwd,
            "fd_equivalent_speedup": 6 * m.n * ms_fwd / ms_grad,
-           "adjoint_tflops": EXEC_FLOPS_PER_PAIR_Q_ADJ * work / (adj_ms / 1e3) / 1e12,
-           "adjoint_flops_per_pair_q": EXEC_FLOPS_PER_PAIR_Q_ADJ,
-           "adjoint_frac_of_peak": EXEC_FLOPS_PER_PAIR_Q_ADJ * work / (adj_ms / 1e3) / 1e12 / PEAK_FP32_TFLOPS,
-           "adjoint_frac_nominal": NOMINAL_FLOPS_PER_PAIR_Q_ADJ * work / (adj_ms / 1e3) / 1e12 / PEAK_FP32_TFLOPS,
            "accuracy": {"target": "seeded perturbed copy, stored oracle profile", "grad_rel_norm_err": e_norm,
                         "grad_worst_atom_err": e_atom, "atoms_checked": int(len(atoms)),
                         "profile_max_rel_err": err_I}}
-    # the same lattice on a 100-point log-spaced grid: direct forward + direct adjoint
+    if ctx.variant() == (0, 0):  # binned: one sweep over the ordered pairs
+        res["adjoint_pairs_per_s"] = m.n * (m.n - 1.0) / (adj_ms / 1e3)
+    else:
+        tflops = EXEC_FLOPS_PER_PAIR_Q_ADJ * work / (adj_ms / 1e3) / 1e12
+        res.update({"adjoint_tflops": tflops, "adjoint_flops_per_pair_q": EXEC_FLOPS_PER_PAIR_Q_ADJ,
+                    "adjoint_frac_of_peak": tflops / PEAK_FP32_TFLOPS,
+                    "adjoint_frac_nominal": tflops * NOMINAL_FLOPS_PER_PAIR_Q_ADJ / EXEC_FLOPS_PER_PAIR_Q_ADJ /
+                    PEAK_FP32_TFLOPS})
+    # the same lattice on a 100-point log-spaced grid
     ql = W.log_grid(1e-3, 0.5, 100)
     tab_l = torch.from_numpy(W.gaussian_table((10.0,), 2.0, ql)).to(dev)
     fwd_l = sd.debye_profile(coords, types, tab_l, ql, ctx=ctx)
