@@ -393,18 +393,23 @@ __global__ __launch_bounds__(kWave) void k_adjoint(AdjArgs a) {
   outi[3 * (lane + kWave) + 2] = g2z;
 }
 
-template <int QA, bool DIRECT>
-__global__ __launch_bounds__(kWave, 2) void k_adjoint_pa(AdjArgs a) {
+// W waves share a strip's J block, a part each.
+template <int QA, bool DIRECT, int W>
+__global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
   static_assert(QA % 4 == 0, "table rows are staged as float4");
-  constexpr int BJ = kAdjPaBJ;
   constexpr int Q4 = QA / 4;
   constexpr int E4 = kPaSub * Q4;  // float4 elements of one run's rows
-  __shared__ double4 sj[kPaSub];
-  __shared__ __align__(16) float fj[kPaSub][QA];
-  __shared__ double gjl[BJ * 3];
-  __shared__ __align__(16) float iql[QA];
+  __shared__ double4 sj_all[W][kPaSub];
+  __shared__ __align__(16) float fj_all[W][kPaSub][QA];
+  __shared__ double gjl_all[kAdjPaBJ * 3];
+  __shared__ __align__(16) float iql_all[W][QA];
+  __shared__ double gi[W][kWave][3];
 
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % kWave;
+  const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  double4* sj = sj_all[wave];
+  float(*fj)[QA] = fj_all[wave];
+  float* iql = iql_all[wave];
   const int64_t t = blockIdx.x;
   const StructDesc d = a.sd.get(0);
   const StripPos sp = decode_strip(t, d.n, a.geo);
@@ -435,16 +440,21 @@ __global__ __launch_bounds__(kWave, 2) void k_adjoint_pa(AdjArgs a) {
   }
 
   double gx = 0.0, gy = 0.0, gz = 0.0;
+  const int bj = a.geo.bj;
+  const int len = bj / W;
+  double* gjl = gjl_all + 3 * len * wave;
 #pragma unroll 1
   for (int J = sp.Ja; J < sp.Jb; ++J) {
-    const int j0 = J * BJ;
-    const int j1 = min(n, j0 + BJ);
-    __syncthreads();
-    for (int k = lane; k < 3 * BJ; k += kWave) gjl[k] = 0.0;
+    const int j0 = J * bj + wave * len;
+    const int j1 = min(n, j0 + len);
+    wave_sync<W>();
+    for (int k = lane; k < 3 * len; k += kWave) gjl[k] = 0.0;
+    // (a part without a pair j > i stores zeros)
+    const int first = j1 <= sp.I * kWave + 1 ? j1 : j0;
 #pragma unroll 1
-    for (int u0 = j0; u0 < j1; u0 += kPaSub) {
+    for (int u0 = first; u0 < j1; u0 += kPaSub) {
       const int ns = min(kPaSub, j1 - u0);
-      __syncthreads();
+      wave_sync<W>();
       const int ty = lane < ns ? clamp_type(a.tsort[d.atom_off + u0 + lane], a.T) : 0;  // row 0 past the run
       if (lane < ns) sj[lane] = a.xyz[d.atom_off + u0 + lane];
       for (int e = lane; e < E4; e += kWave) {
@@ -454,7 +464,7 @@ __global__ __launch_bounds__(kWave, 2) void k_adjoint_pa(AdjArgs a) {
         reinterpret_cast<float4*>(&fj[0][0])[e] =
             *reinterpret_cast<const float4*>(a.tabp + static_cast<int64_t>(tr) * a.ldt + m0 + 4 * c);
       }
-      __syncthreads();
+      wave_sync<W>();
       if constexpr (DIRECT) {
         // per group of four q the product form, the one-FMA reduction or the
         // exact one, chosen from the wave's extremes of 1/r as in k_adjoint;
@@ -621,9 +631,22 @@ __global__ __launch_bounds__(kWave, 2) void k_adjoint_pa(AdjArgs a) {
         }
       }
     }
-    __syncthreads();
-    double* outj = a.gJ + (pidx * a.geo.g * BJ + static_cast<int64_t>(J - sp.Ja) * BJ) * 3;
+    wave_sync<W>();
+    double* outj = a.gJ + (pidx * a.geo.g * bj + static_cast<int64_t>(J - sp.Ja) * bj + wave * len) * 3;
     for (int k = lane; k < 3 * (j1 - j0); k += kWave) outj[k] = gjl[k];
+  }
+  if constexpr (W > 1) {
+    gi[wave][lane][0] = gx;
+    gi[wave][lane][1] = gy;
+    gi[wave][lane][2] = gz;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int p = 1; p < W; ++p) {
+      gx += gi[p][lane][0];
+      gy += gi[p][lane][1];
+      gz += gi[p][lane][2];
+    }
   }
   double* outi = a.gI + pidx * kWave * 3;
   outi[3 * lane + 0] = gx;
@@ -714,23 +737,31 @@ hipError_t launch_adjoint(const AdjArgs& a, int32_t nchunks, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_adjoint_pa(const AdjArgs& a, int32_t nchunks, int32_t qa_template, hipStream_t st) {
-  if (a.n_strips <= 0) return hipSuccess;
-  if (!geometry_ok(a.geo) || a.geo.bj != kAdjPaBJ || a.geo.ib != kWave || a.geo.g != 1 || a.qa > qa_template)
-    return hipErrorInvalidValue;
-  const dim3 grid(static_cast<uint32_t>(a.n_strips), nchunks);
+template <int W>
+hipError_t launch_adjoint_pa_t(const AdjArgs& a, dim3 grid, int32_t qa_template, hipStream_t st) {
+  const dim3 block(W * kWave);
   if (a.qdev) {
     if (qa_template != 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_adjoint_pa<64, true>), grid, dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL((k_adjoint_pa<64, true, W>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   switch (qa_template) {
-    case 32: hipLaunchKernelGGL((k_adjoint_pa<32, false>), grid, dim3(kWave), 0, st, a); break;
-    case 64: hipLaunchKernelGGL((k_adjoint_pa<64, false>), grid, dim3(kWave), 0, st, a); break;
-    case 100: hipLaunchKernelGGL((k_adjoint_pa<100, false>), grid, dim3(kWave), 0, st, a); break;
+    case 32: hipLaunchKernelGGL((k_adjoint_pa<32, false, W>), grid, block, 0, st, a); break;
+    case 64: hipLaunchKernelGGL((k_adjoint_pa<64, false, W>), grid, block, 0, st, a); break;
+    case 100: hipLaunchKernelGGL((k_adjoint_pa<100, false, W>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_adjoint_pa(const AdjArgs& a, int32_t nchunks, int32_t qa_template, hipStream_t st) {
+  if (a.n_strips <= 0) return hipSuccess;
+  if (!geometry_ok(a.geo) || a.geo.bj > kAdjPaBJ || a.geo.bj % (kPaWaves * 2) || a.geo.ib != kWave || a.geo.g != 1 ||
+      a.qa > qa_template)
+    return hipErrorInvalidValue;
+  const dim3 grid(static_cast<uint32_t>(a.n_strips), nchunks);
+  return pa_parts(a.sd.one.n, a.geo, nchunks) == kPaWaves ? launch_adjoint_pa_t<kPaWaves>(a, grid, qa_template, st)
+                                                         : launch_adjoint_pa_t<1>(a, grid, qa_template, st);
 }
 
 hipError_t launch_grad_reduce(const AdjArgs& a, int64_t n, int32_t nchunks, const int32_t* perm, double* grad_out,

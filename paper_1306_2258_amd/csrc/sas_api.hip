@@ -506,9 +506,9 @@ void add_adjoint(Schedule* sc, int64_t n, int32_t Nq) {
 // table covers every chunk's template width.
 void add_adjoint_pa(Schedule* sc, int64_t n, int32_t Nq) {
   sc->grad = true;
-  sc->geo_adj.bj = sas::kAdjPaBJ;
+  sc->geo_adj.bj = n < 2048 ? sas::kWave : sas::kAdjPaBJ;
   sc->geo_adj.ib = sas::kWave;
-  sc->geo_adj.c = sas::kAdjPaBJ / sas::kWave;
+  sc->geo_adj.c = sc->geo_adj.bj / sas::kWave;
   sc->geo_adj.g = 1;
   sc->n_strips_adj = sas::strips_of(n, sc->geo_adj);
   const int32_t cap = sc->direct ? 64 : 100;
@@ -864,14 +864,32 @@ struct RowsLayout {
 // J blocks of at most 512 atoms (the FP32 sum of one block is exact enough,
 // as in the forward), smaller for small structures so that the square still
 // holds about 2048 work-groups.
+// J-block atoms of the square of pairs: the rounds of one wave per SIMD that the
+// nI by n / bj work-groups take, each as long as a block's atoms and the
+// storing and adding of its row (measured as about 20 atoms' time); at least
+// three waves per SIMD where the blocks, of whole runs of kPaSub, allow that.
+int64_t rows_block(int64_t n, int64_t nI) {
+  constexpr int64_t kSimds = 1024, kRow = 20;
+  int64_t best = sas::kPaSub, best_t = INT64_MAX;
+  for (int64_t bj = sas::kPaSub; bj <= 512; bj += sas::kPaSub) {
+    const int64_t waves = nI * ceil_div64(n, bj);
+    if (bj > sas::kPaSub && waves < 5 * kSimds / 2) break;
+    const int64_t t = ceil_div64(waves, kSimds) * (bj + kRow);
+    if (t <= best_t) {
+      best_t = t;
+      best = bj;
+    }
+  }
+  return best;
+}
+
 RowsLayout rows_layout(const sas_ctx* ctx, int64_t n, int32_t T, int32_t Nq, bool direct) {
   RowsLayout R;
   R.sc = make_schedule(ctx, std::vector<int64_t>{n}, T, Nq, 0, 0, direct, true);
   const int64_t nI = std::max<int64_t>(1, ceil_div64(n, sas::kWave));
-  int64_t bj = ceil_div64(n, std::max<int64_t>(1, ceil_div64(2048, nI)));
-  bj = std::min<int64_t>(512, std::max<int64_t>(sas::kWave, ceil_div64(bj, sas::kWave) * sas::kWave));
+  const int64_t bj = rows_block(n, nI);
   R.sc.geo.bj = static_cast<int32_t>(bj);
-  R.sc.geo.c = R.sc.geo.bj / sas::kWave;
+  R.sc.geo.c = 1;  // (the square schedule has no rows of J blocks to skip)
   R.sc.geo.g = 1;
   R.nJ = static_cast<int32_t>(std::max<int64_t>(1, ceil_div64(n, bj)));
   while (R.end_bit < 31 && (int64_t(1) << R.end_bit) < T) ++R.end_bit;

@@ -73,7 +73,15 @@ struct ForwardArgs {
 };
 
 constexpr int kAdjQ = 512;  // q values per adjoint chunk (weights staged in LDS)
-constexpr int kAdjPaBJ = 128; // J-block atoms of the per-atom adjoint
+constexpr int kAdjPaBJ = 128; // J-block atoms of the per-atom adjoint, at most
+
+// Parts a J block of the per-atom form is summed in, each with FP32 sums of its
+// own: kPaWaves, one per wave of a work-group, where the strips alone would
+// leave the chip idle or its last round nearly empty.  A structure's parts
+// depend on it and the tile shape alone (not on its batch), so a forced shape
+// reproduces a call's bits.
+constexpr int kPaWaves = 4;
+constexpr int64_t kPaFewStrips = 8192;
 
 struct AdjArgs {
   DescView sd;          // one structure

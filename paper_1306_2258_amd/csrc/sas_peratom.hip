@@ -58,10 +58,21 @@ __global__ __launch_bounds__(256) void k_atom_sums(DescView sd, const int32_t* _
   const int m = blockIdx.y * kWave + lane;
   const int64_t first = (b - d.pack_off) * kPackBlock + w * kWave;
   double f1 = 0.0, f2 = 0.0;
-  if (m < Nq) {
-    for (int k = 0; k < kWave && first + k < d.n; ++k) {
-      const int t = clamp_type(tsort[d.atom_off + first + k], T);
-      const double f = tabp[static_cast<int64_t>(t) * ldt + m];
+  // (lane k holds atom k's type, so that the rows' loads depend on no other:
+  // sixteen in flight; one after the other they took 27 us at any size)
+  const int count = static_cast<int>(min<int64_t>(kWave, max<int64_t>(0, d.n - first)));
+  const int mine = lane < count ? clamp_type(tsort[d.atom_off + first + lane], T) : 0;
+  const int mc = min(m, Nq - 1);
+  for (int k0 = 0; k0 < count; k0 += 16) {
+    float v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int t = __builtin_amdgcn_readlane(mine, k0 + k);  // (row 0 past the end)
+      v[k] = tabp[static_cast<int64_t>(t) * ldt + mc];
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const double f = k0 + k < count ? static_cast<double>(v[k]) : 0.0;
       f1 += f;
       f2 = fma(f, f, f2);
     }
@@ -81,18 +92,24 @@ __global__ __launch_bounds__(256) void k_atom_sums(DescView sd, const int32_t* _
 }
 
 
-template <int QC, bool DIRECT, bool ROWS>
-__global__ __launch_bounds__(kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_forward_pa(ForwardArgs a) {
+// W waves share a strip's J block, a part each (W = 1: one wave takes every part
+// in turn, with the same sums).
+template <int QC, bool DIRECT, bool ROWS, int W>
+__global__ __launch_bounds__(W * kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_forward_pa(ForwardArgs a) {
   constexpr int NG = QC / kWave;
   constexpr int R = QC % kWave;
   constexpr int NT = NG + (R ? 1 : 0);
   static_assert(QC % 4 == 0, "table rows are staged as float4");
   constexpr int Q4 = QC / 4;
   constexpr int E4 = kPaSub * Q4;  // float4 elements of one run's rows
-  __shared__ double4 sj[kPaSub];
-  __shared__ __align__(16) float fj[kPaSub][QC];
-  __shared__ double tot[NT][kWave];
-  const int lane = threadIdx.x;
+  __shared__ double4 sj_all[W][kPaSub];
+  __shared__ __align__(16) float fj_all[W][kPaSub][QC];
+  __shared__ double tot_all[W][NT][kWave];
+  const int lane = threadIdx.x % kWave;
+  const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  double4* sj = sj_all[wave];
+  float(*fj)[QC] = fj_all[wave];
+  double(*tot)[kWave] = tot_all[wave];
   const int64_t t = blockIdx.x;
   const int s = ROWS ? 0 : find_struct_by_strip(a.sd, t);
   const StructDesc d = a.sd.get(s);
@@ -125,10 +142,14 @@ __global__ __launch_bounds__(kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_forw
   if constexpr (DIRECT) frange = frac_range(chunk_q_lo(a.qdev + m0, nqc), a.qdev[m0 + nqc - 1]);
 
   const int bj = a.geo.bj;
+  const int parts = ROWS ? 1 : pa_parts(n, a.geo, gridDim.y);
+  const int len = bj / parts;
 #pragma unroll 1
-  for (int J = sp.Ja; J < sp.Jb; ++J) {
-    const int j0 = J * bj;
-    const int j1 = min(n, j0 + bj);
+  for (int k = sp.Ja * parts + wave; k < sp.Jb * parts; k += W) {
+    const int J = k / parts;
+    const int j0 = k * len;
+    const int j1 = min(n, j0 + len);
+    if (!ROWS && j1 <= sp.I * kWave + 1) continue;  // (no pair j > i)
     float acc[QC];
 #pragma unroll
     for (int m = 0; m < QC; ++m) acc[m] = 0.f;
@@ -139,7 +160,7 @@ __global__ __launch_bounds__(kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_forw
       // padded table has ldt >= m0 + QC columns, zero beyond Nq; ldt and m0
       // are multiples of 4).  Lane r < ns fetches row r's type; every lane
       // then issues its share of float4 loads at once.
-      __syncthreads();
+      wave_sync<W>();
       const int ty = lane < ns ? clamp_type(a.tsort[d.atom_off + u0 + lane], a.T) : 0;  // row 0 past the run
       if (lane < ns) sj[lane] = a.xyz[d.atom_off + u0 + lane];
       constexpr int K4 = (E4 + kWave - 1) / kWave;  // float4 loads per lane
@@ -164,14 +185,16 @@ __global__ __launch_bounds__(kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_forw
           reinterpret_cast<float4*>(&fj[0][0])[e] = v[k];
         }
       }
-      __syncthreads();
+      wave_sync<W>();
       if constexpr (DIRECT) {
         // the one-FMA reduction for pairs whose lanes all admit it over the
         // chunk; the rest are listed, for the product form or the exact
         // reduction, and summed after the run (one accumulating path per
         // loop, as in the type form; q through the scalar cache as there)
-        __shared__ int slow[DIRECT ? kPaSub : 1];
-        __shared__ int near[DIRECT ? kPaSub : 1];
+        __shared__ int slow_all[W][DIRECT ? kPaSub : 1];
+        __shared__ int near_all[W][DIRECT ? kPaSub : 1];
+        int* slow = slow_all[wave];
+        int* near = near_all[wave];
         int nslow = 0, nnear = 0;
         float kScale31 = 0x1p-31f;  // (held in a VGPR: see the one-FMA reduction)
         asm volatile("" : "+v"(kScale31));
@@ -322,11 +345,16 @@ __global__ __launch_bounds__(kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_forw
     }
   }
   if constexpr (!ROWS) {
+    if (W > 1) __syncthreads();
     double* out = a.partial + t * a.Nq + m0;
+    if (wave != 0) return;
 #pragma unroll
     for (int g = 0; g < NT; ++g) {
       const int m = g * kWave + lane;
-      if (m < nqc) out[m] = tot[g][lane];
+      double v = tot_all[0][g][lane];
+#pragma unroll
+      for (int p = 1; p < W; ++p) v += tot_all[p][g][lane];
+      if (m < nqc) out[m] = v;
     }
   }
 }
@@ -353,21 +381,21 @@ hipError_t launch_atom_sums(const DescView& sd, int64_t n_pack_blocks, const int
   return hipGetLastError();
 }
 
-template <bool ROWS>
+template <bool ROWS, int W>
 hipError_t launch_forward_pa_t(const ForwardArgs& a, dim3 grid, int32_t qc_template, hipStream_t st) {
-  if (!geometry_ok(a.geo)) return hipErrorInvalidValue;
+  const dim3 block(W * kWave);
   if (a.qdev) {
     if (qc_template != 32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_forward_pa<32, true, ROWS>), grid, dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL((k_forward_pa<32, true, ROWS, W>), grid, block, 0, st, a);
     return hipGetLastError();
   }
   switch (qc_template) {
-    case 16: hipLaunchKernelGGL((k_forward_pa<16, false, ROWS>), grid, dim3(kWave), 0, st, a); break;
-    case 32: hipLaunchKernelGGL((k_forward_pa<32, false, ROWS>), grid, dim3(kWave), 0, st, a); break;
-    case 64: hipLaunchKernelGGL((k_forward_pa<64, false, ROWS>), grid, dim3(kWave), 0, st, a); break;
-    case 100: hipLaunchKernelGGL((k_forward_pa<100, false, ROWS>), grid, dim3(kWave), 0, st, a); break;
-    case 128: hipLaunchKernelGGL((k_forward_pa<128, false, ROWS>), grid, dim3(kWave), 0, st, a); break;
-    case 200: hipLaunchKernelGGL((k_forward_pa<200, false, ROWS>), grid, dim3(kWave), 0, st, a); break;
+    case 16: hipLaunchKernelGGL((k_forward_pa<16, false, ROWS, W>), grid, block, 0, st, a); break;
+    case 32: hipLaunchKernelGGL((k_forward_pa<32, false, ROWS, W>), grid, block, 0, st, a); break;
+    case 64: hipLaunchKernelGGL((k_forward_pa<64, false, ROWS, W>), grid, block, 0, st, a); break;
+    case 100: hipLaunchKernelGGL((k_forward_pa<100, false, ROWS, W>), grid, block, 0, st, a); break;
+    case 128: hipLaunchKernelGGL((k_forward_pa<128, false, ROWS, W>), grid, block, 0, st, a); break;
+    case 200: hipLaunchKernelGGL((k_forward_pa<200, false, ROWS, W>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -376,15 +404,21 @@ hipError_t launch_forward_pa_t(const ForwardArgs& a, dim3 grid, int32_t qc_templ
 hipError_t launch_forward_pa(const ForwardArgs& a, int64_t n_strips_total, int32_t qc_template, hipStream_t st) {
   if (n_strips_total <= 0) return hipSuccess;
   const int nchunks = static_cast<int>(ceil_div(a.Nq, a.qc));
-  return launch_forward_pa_t<false>(a, dim3(static_cast<uint32_t>(n_strips_total), nchunks), qc_template, st);
+  if (!geometry_ok(a.geo) || a.geo.bj % (kPaWaves * 2)) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<uint32_t>(n_strips_total), nchunks);
+  // (a batch has strips enough: one wave each; its structures keep their parts)
+  return a.sd.S == 1 && a.geo.g == 1 && pa_parts(a.sd.one.n, a.geo, nchunks) == kPaWaves
+             ? launch_forward_pa_t<false, kPaWaves>(a, grid, qc_template, st)
+             : launch_forward_pa_t<false, 1>(a, grid, qc_template, st);
 }
 
 hipError_t launch_forward_pa_rows(const ForwardArgs& a, int32_t qc_template, hipStream_t st) {
   const StructDesc d = a.sd.one;
   if (d.n <= 0) return hipSuccess;
+  if (a.geo.bj <= 0) return hipErrorInvalidValue;
   const int64_t blocks = ceil_div(d.n, kWave) * ceil_div(d.n, a.geo.bj);
   const int nchunks = static_cast<int>(ceil_div(a.Nq, a.qc));
-  return launch_forward_pa_t<true>(a, dim3(static_cast<uint32_t>(blocks), nchunks), qc_template, st);
+  return launch_forward_pa_t<true, 1>(a, dim3(static_cast<uint32_t>(blocks), nchunks), qc_template, st);
 }
 
 }  // namespace sas

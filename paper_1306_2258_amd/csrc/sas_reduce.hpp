@@ -27,8 +27,11 @@ __device__ __forceinline__ void reduce_slice(const DescView& sd, int64_t sl, con
   for (int g = blockIdx.y; g < groups; g += gridDim.y) {  // (grid.y is capped at 65535)
     const int m = g * kWave + lane;
     double acc = 0.0;
-    if (m < Nq)
+    if (m < Nq) {
+      // (sixteen loads in flight: one at a time took 20 us for 2,250 strips)
+#pragma unroll 16
       for (int64_t t = a; t < b; ++t) acc += partial[t * Nq + m];
+    }
     __syncthreads();
     part[w][lane] = acc;
     __syncthreads();
@@ -76,6 +79,7 @@ __device__ __forceinline__ void reduce_final(const DescView& sd, int s, int g, c
 #pragma unroll 16
       for (int k = 0; k < mine; ++k) pairs += read_sum<AGENT>(prows + static_cast<int64_t>(k) * Nq + m);
     } else {
+#pragma unroll 8
       for (int64_t k = w; k < d.n_slices; k += 4) pairs += read_sum<AGENT>(slice_sums + (d.slice_off + k) * Nq + m);
     }
   }
@@ -87,6 +91,7 @@ __device__ __forceinline__ void reduce_final(const DescView& sd, int s, int g, c
     if (qm == 0.0) {
       double f = 0.0;
       if (asum) {
+#pragma unroll 16
         for (int64_t k = 0; k < nb; ++k) f += asum[((d.pack_off + k) * 2 + 0) * Nq + m];
       } else {
         for (int t = 0; t < T; ++t)
@@ -97,6 +102,7 @@ __device__ __forceinline__ void reduce_final(const DescView& sd, int s, int g, c
       const double psum = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
       double diag = 0.0;
       if (asum) {
+#pragma unroll 16
         for (int64_t k = 0; k < nb; ++k) diag += asum[((d.pack_off + k) * 2 + 1) * Nq + m];
       } else {
         for (int t = 0; t < T; ++t) {

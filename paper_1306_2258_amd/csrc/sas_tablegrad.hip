@@ -118,6 +118,7 @@ hipError_t launch_table_grad_final(int64_t n_slices, const double* gslices, cons
 __global__ void k_rows_f0(const double* __restrict__ asum, int64_t n_pack, int32_t Nq, double* __restrict__ f0) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   double s = 0.0;
+#pragma unroll 16
   for (int64_t b = 0; b < n_pack; ++b) s += asum[(b * 2 + 0) * Nq];
   f0[0] = s;
 }
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(kRowsAtoms) void k_rows_final(const float* __restri
 #pragma unroll
     for (int g = 0; g < 4; ++g) col[g] = rows + static_cast<int64_t>(min(m0 + g, Nq - 1)) * n + i;
     const int64_t jstride = static_cast<int64_t>(rows_ld) * n;
-#pragma unroll 4
+#pragma unroll 8
     for (int J = 0; J < nJ; ++J) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) r[g] += static_cast<double>(col[g][J * jstride]);
