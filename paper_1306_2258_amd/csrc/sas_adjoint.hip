@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kWave) void k_adjoint(AdjArgs a) {
 
 // W waves share a strip's J block, a part each.
 template <int QA, bool DIRECT, int W>
-__global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
+__global__ __launch_bounds__(W * kWave, DIRECT ? 3 : 2) void k_adjoint_pa(AdjArgs a) {
   static_assert(QA % 4 == 0, "table rows are staged as float4");
   constexpr int Q4 = QA / 4;
   constexpr int E4 = kPaSub * Q4;  // float4 elements of one run's rows
@@ -403,13 +403,15 @@ __global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
   __shared__ __align__(16) float fj_all[W][kPaSub][QA];
   __shared__ double gjl_all[kAdjPaBJ * 3];
   __shared__ __align__(16) float iql_all[W][QA];
-  __shared__ double gi[W][kWave][3];
+  __shared__ double wl_all[W][QA];
+  __shared__ double gi[W > 1 ? W : 1][kWave][3];
 
   const int lane = threadIdx.x % kWave;
   const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   double4* sj = sj_all[wave];
   float(*fj)[QA] = fj_all[wave];
   float* iql = iql_all[wave];
+  double* wl = wl_all[wave];
   const int64_t t = blockIdx.x;
   const StructDesc d = a.sd.get(0);
   const StripPos sp = decode_strip(t, d.n, a.geo);
@@ -426,18 +428,31 @@ __global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
   const double dq = a.dq;
   const int64_t pidx = static_cast<int64_t>(blockIdx.y) * a.n_strips + t;
   // this lane's weights w_m f_i(q_m) (zero at q = 0, where I does not depend
-  // on the positions, and past the chunk) and the chunk's 1/q_m
-  float wi[QA];
-  const float* fi = a.tabp + static_cast<int64_t>(ti) * a.ldt + m0;
-#pragma unroll
-  for (int m = 0; m < QA; ++m) {
-    const double qm = m < nqa ? (DIRECT ? a.qdev[m0 + m] : a.q0 + (m0 + m) * dq) : 0.0;
-    wi[m] = qm > 0.0 ? static_cast<float>(a.w[m0 + m] * static_cast<double>(fi[m])) : 0.f;
-  }
+  // on the positions, and past the chunk) and the chunk's 1/q_m.  (The weights
+  // go through LDS and the row comes in 16-byte loads, all in flight: a load
+  // and a branch per q took longer than the pairs of a short part.)
   for (int m = lane; m < QA; m += kWave) {
     const double qm = m < nqa ? (DIRECT ? a.qdev[m0 + m] : a.q0 + (m0 + m) * dq) : 0.0;
     iql[m] = qm > 0.0 ? static_cast<float>(1.0 / qm) : 0.f;
+    wl[m] = qm > 0.0 ? a.w[m0 + m] : 0.0;
   }
+  float wi[QA];
+  const float* fi = a.tabp + static_cast<int64_t>(ti) * a.ldt + m0;
+#pragma unroll
+  for (int c = 0; c < Q4; ++c) {
+    const float4 f4 = reinterpret_cast<const float4*>(fi)[c];
+    wi[4 * c] = f4.x;
+    wi[4 * c + 1] = f4.y;
+    wi[4 * c + 2] = f4.z;
+    wi[4 * c + 3] = f4.w;
+  }
+  wave_sync();
+#pragma unroll
+  for (int m = 0; m < QA; ++m) {
+    if (m % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // (four at a time: registers)
+    wi[m] = static_cast<float>(wl[m] * static_cast<double>(wi[m]));
+  }
+  if (!((DIRECT ? a.qdev[m0] : a.q0 + m0 * dq) > 0.0)) wi[0] = 0.f;
 
   double gx = 0.0, gy = 0.0, gz = 0.0;
   const int bj = a.geo.bj;
@@ -447,14 +462,14 @@ __global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
   for (int J = sp.Ja; J < sp.Jb; ++J) {
     const int j0 = J * bj + wave * len;
     const int j1 = min(n, j0 + len);
-    wave_sync<W>();
+    wave_sync();
     for (int k = lane; k < 3 * len; k += kWave) gjl[k] = 0.0;
     // (a part without a pair j > i stores zeros)
     const int first = j1 <= sp.I * kWave + 1 ? j1 : j0;
 #pragma unroll 1
     for (int u0 = first; u0 < j1; u0 += kPaSub) {
       const int ns = min(kPaSub, j1 - u0);
-      wave_sync<W>();
+      wave_sync();
       const int ty = lane < ns ? clamp_type(a.tsort[d.atom_off + u0 + lane], a.T) : 0;  // row 0 past the run
       if (lane < ns) sj[lane] = a.xyz[d.atom_off + u0 + lane];
       for (int e = lane; e < E4; e += kWave) {
@@ -464,7 +479,7 @@ __global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
         reinterpret_cast<float4*>(&fj[0][0])[e] =
             *reinterpret_cast<const float4*>(a.tabp + static_cast<int64_t>(tr) * a.ldt + m0 + 4 * c);
       }
-      wave_sync<W>();
+      wave_sync();
       if constexpr (DIRECT) {
         // per group of four q the product form, the one-FMA reduction or the
         // exact one, chosen from the wave's extremes of 1/r as in k_adjoint;
@@ -631,7 +646,7 @@ __global__ __launch_bounds__(W * kWave, 2) void k_adjoint_pa(AdjArgs a) {
         }
       }
     }
-    wave_sync<W>();
+    wave_sync();
     double* outj = a.gJ + (pidx * a.geo.g * bj + static_cast<int64_t>(J - sp.Ja) * bj + wave * len) * 3;
     for (int k = lane; k < 3 * (j1 - j0); k += kWave) outj[k] = gjl[k];
   }

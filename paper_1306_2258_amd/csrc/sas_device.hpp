@@ -382,17 +382,12 @@ __device__ __forceinline__ bool frac_reduction_ok(const FracRange& fr, double r2
   return w == 0.f || (r2 >= fr.r2_lo && r2 < fr.r2_hi);
 }
 
-// Orders one wave's LDS accesses (which the hardware keeps in order) where the
-// waves of a work-group of W each use LDS of their own.
-template <int W>
+// Orders one wave's LDS accesses (which the hardware keeps in order) where each
+// wave of a work-group uses LDS of its own.
 __device__ __forceinline__ void wave_sync() {
-  if constexpr (W == 1) {
-    __syncthreads();
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 }  // namespace sas

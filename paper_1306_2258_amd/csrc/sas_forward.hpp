@@ -172,4 +172,28 @@ __device__ __forceinline__ float lane_allreduce_tail(float* acc, int lane) {
   return mine;
 }
 
+// The same by recursive halving, padded to a power of two: P - 1 exchanges and
+// one for each lane bit above, instead of 6 R (R = 36: 63 for 216, which cost
+// a part of 32 J atoms a tenth of its time).
+template <int R>
+__device__ __forceinline__ float lane_halving_tail(const float* acc, int lane) {
+  constexpr int P = R <= 4 ? 4 : (R <= 8 ? 8 : (R <= 16 ? 16 : (R <= 32 ? 32 : 64)));
+  float v[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) v[k] = k < R ? acc[k] : 0.f;
+#pragma unroll
+  for (int half = P / 2; half >= 1; half >>= 1) {
+    const bool up = (lane & half) != 0;
+#pragma unroll
+    for (int k = 0; k < half; ++k) {
+      const float send = up ? v[k] : v[k + half];
+      const float keep = up ? v[k + half] : v[k];
+      v[k] = keep + __shfl_xor(send, half, kWave);
+    }
+  }
+#pragma unroll
+  for (int off = P; off < kWave; off <<= 1) v[0] += __shfl_xor(v[0], off, kWave);
+  return v[0];
+}
+
 }  // namespace sas

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(W * kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_
       // padded table has ldt >= m0 + QC columns, zero beyond Nq; ldt and m0
       // are multiples of 4).  Lane r < ns fetches row r's type; every lane
       // then issues its share of float4 loads at once.
-      wave_sync<W>();
+      wave_sync();
       const int ty = lane < ns ? clamp_type(a.tsort[d.atom_off + u0 + lane], a.T) : 0;  // row 0 past the run
       if (lane < ns) sj[lane] = a.xyz[d.atom_off + u0 + lane];
       constexpr int K4 = (E4 + kWave - 1) / kWave;  // float4 loads per lane
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(W * kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_
           reinterpret_cast<float4*>(&fj[0][0])[e] = v[k];
         }
       }
-      wave_sync<W>();
+      wave_sync();
       if constexpr (DIRECT) {
         // the one-FMA reduction for pairs whose lanes all admit it over the
         // chunk; the rest are listed, for the product form or the exact
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(W * kWave, DIRECT ? 4 : (QC > 128 ? 2 : 3)) void k_
       tot[g][lane] += static_cast<double>(v);
     }
     if constexpr (R > 0) {
-      const float v = lane_allreduce_tail<R>(acc + NG * kWave, lane);
+      const float v = R > 32 ? lane_halving_tail<R>(acc + NG * kWave, lane) : lane_allreduce_tail<R>(acc + NG * kWave, lane);
       tot[NG][lane] += static_cast<double>(v);
     }
   }

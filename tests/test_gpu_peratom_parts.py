@@ -1,0 +1,74 @@
+"""The per-atom form where its J blocks are shared by four waves, at the edges of
+the parts and where the block length or the number of parts changes.
+
+Profiles within 1e-6 of the FP64 oracle, gradients within 1e-5 in norm and at the
+worst atom: the bounds of tests/test_gpu_peratom.py and tests/gradcheck.py."""
+from __future__ import annotations
+
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from tests.gradcheck import GTOL, assert_grad_close
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-6
+
+
+@pytest.fixture(scope="module")
+def sd():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1306_2258_amd as mod
+
+    return mod
+
+
+def dev(m):
+    import torch
+
+    return (torch.from_numpy(m.coords).cuda(), torch.from_numpy(m.types).cuda(), torch.from_numpy(m.table).cuda())
+
+
+def close(got, ref):
+    assert np.max(np.abs(got - ref) / np.abs(ref)) <= TOL
+
+
+# parts of 16 atoms (J blocks of 64) and of 32 (from 2,048 atoms); chunks whose
+# last reduction is padded (36 of 100 q) and those whose is not; both evaluations
+@pytest.mark.parametrize("n", [2, 15, 17, 63, 65, 130, 2047, 2049])
+@pytest.mark.parametrize("nq,grid", [(100, "uniform"), (20, "uniform"), (33, "log")])
+def test_parts_of_one_molecule(sd, n, nq, grid):
+    import torch
+
+    print(f"[case] per-atom N={n} Nq={nq} {grid}", flush=True)
+    sys.stdout.flush()
+    q = W.log_grid(1e-3, 0.8, nq) if grid == "log" else None
+    m = W.with_per_atom_factors(W.random_molecule(9000 + n, n, nq, q1=0.8, extent=3.0 * n ** (1 / 3) + 2.0, q=q), 9100 + n)
+    ctx = sd.Context(0)
+    ctx.set_form("per_atom")
+    w = np.random.default_rng(n).normal(size=nq)
+    wd = torch.from_numpy(w).cuda()
+    close(sd.debye_profile(*dev(m), m.q, ctx=ctx).cpu().numpy(), oracle.profile(m.coords, m.types, m.table, m.q))
+    g = sd.debye_grad(*dev(m), m.q, wd, ctx=ctx).cpu().numpy()
+    pick = np.unique(np.linspace(0, n - 1, min(n, 200)).astype(np.int64))
+    assert_grad_close(g[pick], oracle.grad(m.coords, m.types, m.table, m.q, w, atoms=pick), GTOL, f"N={n}")
+    t = sd.debye_grad_table(*dev(m), m.q, wd, ctx=ctx).cpu().numpy()
+    ref = oracle.grad_table(m.coords, m.types, m.table, m.q, w)
+    assert np.linalg.norm(t - ref) <= GTOL * np.linalg.norm(ref)
+
+
+# 8,192 strips of 128 atoms: about 11,500 atoms; sampled q
+@pytest.mark.parametrize("n", [11400, 11700])
+def test_where_the_parts_end(sd, n):
+    print(f"[case] per-atom N={n}", flush=True)
+    m = W.with_per_atom_factors(W.random_molecule(9200, n, 16, q1=0.6, extent=60.0), 9300)
+    got = sd.debye_profile(*dev(m), m.q).cpu().numpy()
+    pick = np.array([0, 1, 7, 15])
+    close(got[pick], oracle.profile(m.coords, m.types, np.ascontiguousarray(m.table[:, pick]), m.q[pick]))
