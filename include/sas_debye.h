@@ -40,14 +40,23 @@
  *  - The q grid is host double [nq], finite, q_0 >= 0 and strictly
  *    increasing.  A uniform grid (q_m = q_0 + m dq within 8 ulp of max q; the
  *    Results section evaluates profiles on such grids; Nq <= 2 always counts
- *    as uniform) takes the fast path: the pair kernel steps sin(q r) from one
- *    q to the next by a recurrence.  Any other grid is evaluated directly,
- *    one sine per pair and q, at a few times the cost per pair and q.  Every
- *    call accepts both.
- *  - Results are FP64.  Pair terms are evaluated in FP32 from FP64 per-pair
- *    set-up values; every cross-lane and cross-block sum beyond one 64-lane
- *    wave is FP64 and in a fixed order, so two identical calls give bitwise
- *    identical results.
+ *    as uniform) takes the recurrence where the sums below are not binned: the
+ *    pair kernel steps sin(q r) from one q to the next.  Any other grid is then
+ *    evaluated directly, one sine per pair and q, at a few times the cost per
+ *    pair and q.  Every call accepts both.
+ *  - Binned sums: with few types (T <= 64), Nq >= 8 and enough atoms (129 on a
+ *    uniform grid, 302 on any other), and no shape or direct form forced, each
+ *    pair's FP64 distance is deposited once, as powers of its position in a
+ *    narrow bin of r^2 (exact integer sums), and the bins are turned into I(q)
+ *    by a polynomial of degree 5 in r^2 per bin: the cost of a pair does not
+ *    depend on Nq or on the grid.  The device decides per structure from its
+ *    extent: a structure too long or sparse for the bins to pay, or with a
+ *    coordinate that is not finite, takes the recurrence or the direct form
+ *    in the same call.
+ *  - Results are FP64.  Pair terms of the other forms are evaluated in FP32 from
+ *    FP64 per-pair set-up values; every cross-lane and cross-block sum beyond one
+ *    64-lane wave is FP64 and in a fixed order (or exact), so two identical
+ *    calls give bitwise identical results.
  *  - Errors: a status code, plus a thread-local message from
  *    sas_last_error().  Host-detectable argument errors are reported before
  *    any device work is enqueued and leave the outputs untouched.  Device-side
@@ -307,7 +316,8 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
  * at most 32).  Returns SAS_ERR_INVALID_ARG for other values.
  * sas_get_variant reports the shape the last forward call (or plan) used;
  * passing it back to sas_set_variant reproduces that call's chunks, and so
- * its results bit for bit.
+ * its results bit for bit.  Binned sums have no tile shape: they report (0, 0),
+ * the automatic setting; any other shape turns them off.
  */
 sas_status sas_set_variant(sas_ctx* ctx, int32_t bj, int32_t qc);
 sas_status sas_get_variant(const sas_ctx* ctx, int32_t* bj, int32_t* qc);
@@ -320,7 +330,8 @@ sas_status sas_get_variant(const sas_ctx* ctx, int32_t* bj, int32_t* qc);
  * directly, one sine per pair and q as in the paper's per-q kernel
  * (Implementation section), which measures what the recurrence saves.
  * SAS_FORM_PER_ATOM weights every pair term by f_j inside the q loop even
- * for few types.  The pair kernel of the recurrence's type form has two
+ * for few types.  Both turn binned sums off; otherwise the form reported for a
+ * binned call is the one its structures would take without the bins.  The pair kernel of the recurrence's type form has two
  * launches with bitwise the same results: a grid of one work-group per strip
  * of pair tiles, and a persistent grid (as many one-wave work-groups as the
  * GPU holds at once, each pulling the next strip from a counter in the

@@ -1728,37 +1728,37 @@ bool orient_rot(const double* q, int32_t nq_o, double r_max, double* dq) {
 }
 
 // Gauss-Legendre rule of n points on [-1, 1]: roots of P_n by Newton's method
-// from cos(pi (i + 3/4) / (n + 1/2)), P_n and P_n' from the three-term
-// recurrence, weights 2 / ((1 - x^2) P_n'(x)^2).
+// from (1 - (n - 1) / (8 n^3)) cos(pi (i + 3/4) / (n + 1/2)) (Tricomi's
+// approximation), P_n and P_n' from the three-term recurrence with its factors
+// formed once, weights 2 / ((1 - x^2) P_n'(x)^2).
 void gauss_legendre(int n, double* x, double* w) {
+  std::vector<double> a(n + 1), b(n + 1);
+  for (int k = 2; k <= n; ++k) {
+    a[k] = (2.0 * k - 1.0) / k;
+    b[k] = (k - 1.0) / k;
+  }
+  const double nn = n;
+  const double shrink = 1.0 - (nn - 1.0) / (8.0 * nn * nn * nn);
   for (int i = 0; i < (n + 1) / 2; ++i) {
-    double z = std::cos(3.14159265358979323846 * (i + 0.75) / (n + 0.5));
-    double dp = 1.0;
-    for (int it = 0; it < 100; ++it) {
+    double z = shrink * std::cos(3.14159265358979323846 * (i + 0.75) / (n + 0.5));
+    double p = 0.0, dp = 1.0;
+    auto legendre = [&] {
       double p0 = 1.0, p1 = z;
       for (int k = 2; k <= n; ++k) {
-        const double p2 = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
+        const double p2 = a[k] * z * p1 - b[k] * p0;
         p0 = p1;
         p1 = p2;
       }
-      if (n == 1) p0 = 1.0;
+      p = p1;
       dp = n * (z * p1 - p0) / (z * z - 1.0);
-      const double dz = p1 / dp;
+    };
+    for (int it = 0; it < 100; ++it) {
+      legendre();
+      const double dz = p / dp;
       z -= dz;
-      if (std::fabs(dz) <= 1e-15 * std::fmax(1.0, std::fabs(z))) {
-        // derivative at the converged root for the weight
-        p0 = 1.0;
-        p1 = z;
-        for (int k = 2; k <= n; ++k) {
-          const double p2 = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
-          p0 = p1;
-          p1 = p2;
-        }
-        if (n == 1) p0 = 1.0;
-        dp = n * (z * p1 - p0) / (z * z - 1.0);
-        break;
-      }
+      if (std::fabs(dz) <= 1e-15 * std::fmax(1.0, std::fabs(z))) break;
     }
+    legendre();  // the derivative at the root, for the weight
     x[i] = -z;
     x[n - 1 - i] = z;
     w[i] = w[n - 1 - i] = 2.0 / ((1.0 - z * z) * dp * dp);
@@ -1838,11 +1838,13 @@ OrientPlan plan_orient(int64_t n, const double* q, int32_t nq_o, double r_max, d
   p.gl.resize(2 * static_cast<size_t>(nodes));
   p.total_blocks = blk;
   // at most kOrientBlocksTarget work-groups (the workspace bound) of at least
-  // 256 atoms for the whole rule; the half takes no more room than that
+  // 256 atoms for the whole rule; the half takes no more room than that, and
+  // parts of 128 atoms (a small molecule's work-groups do not fill the chip, and
+  // the kernel takes as long as one part)
   const int64_t by_atoms = cdiv(n, int64_t(256));
   const int64_t rule_parts = best_parts(
       rule_blk, std::max<int64_t>(1, std::min(by_atoms, cdiv(kOrientBlocksTarget, std::max<int64_t>(rule_blk, 1)))), slots);
-  const int64_t most = std::max<int64_t>(1, std::min(by_atoms, rule_parts * rule_dirs / std::max<int64_t>(dirs, 1)));
+  const int64_t most = std::max<int64_t>(1, std::min(cdiv(n, int64_t(128)), rule_parts * rule_dirs / std::max<int64_t>(dirs, 1)));
   p.parts = static_cast<int32_t>(best_parts(blk, most, slots));
   p.atoms_per_part = static_cast<int32_t>(cdiv(cdiv(std::max<int64_t>(n, 1), int64_t(p.parts)),
                                                         int64_t(sas::kPaSub)) * sas::kPaSub);
@@ -1863,6 +1865,10 @@ void fill_rules(OrientPlan* p) {
     std::vector<double> x(nodes), w(nodes);
     gauss_legendre(nodes, x.data(), w.data());
     double* to = p->gl.data() + 2 * static_cast<size_t>(p->chunks[c].gl_off);
+    if (c > 0 && p->degree[c] == p->degree[c - 1]) {
+      std::copy_n(p->gl.data() + 2 * static_cast<size_t>(p->chunks[c - 1].gl_off), 2 * half, to);
+      continue;
+    }
     for (int32_t i = 0; i < half; ++i) {
       const int32_t k = nodes - half + i;
       const bool middle = 2 * k + 1 == nodes;
@@ -2085,25 +2091,7 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     join.ev = ctx->join_ev;
   }
 
-  // 3. direct sum for the rest, on a compact copy of their table columns (first,
-  //    so that the GPU has work while the host computes the quadrature)
-  if (nq_d > 0) {
-    QGrid gd;
-    st = classify_q(q + nq_o, nq_d, &gd);
-    if (st != SAS_OK) return st;
-    float* tabd = reinterpret_cast<float*>(w + L.tabd);
-    SAS_HIP(sas::launch_copy_cols(table, t, nq, nq_o, nq_d, nq_d, tabd, hd));
-    const Schedule sd = type_schedule(ctx, std::vector<int64_t>{n}, t, nq_d, q[nq - 1], !gd.uniform || ctx->force_direct,
-                                      use_per_atom(ctx, t, n), 0, kBinPoolHybrid);
-    const Layout Ld = make_layout(sd, t, nq_d);
-    void* wd = w + L.direct;
-    st = stage_upload(ctx, wd, Ld, upload_image(sd, Ld, gd), hd);
-    if (st != SAS_OK) return st;
-    st = enqueue_forward(ctx, sd, Ld, coords, types, tabd, t, nq_d, gd.q0, gd.dq, I_out + nq_o, wd, hd);
-    if (st != SAS_OK) return st;
-  }
-
-  // 4. orientation average of the leading q values
+  // 3. orientation average of the leading q values
   if (nq_o > 0) {
     fill_rules(&plan);
     std::vector<char> img(L.upload_bytes, 0);
@@ -2132,6 +2120,23 @@ sas_status sas_debye_profile_hybrid(sas_ctx* ctx, const float* coords, const int
     a.ored = reinterpret_cast<double*>(w + L.ored);
     a.rot = orient_rot(q, nq_o, r_max, &a.dq) ? 1 : 0;
     SAS_HIP(sas::launch_orient(a, plan.total_blocks, nq_o, I_out, hs));
+  }
+
+  // 4. direct sum for the rest, on a compact copy of their table columns
+  if (nq_d > 0) {
+    QGrid gd;
+    st = classify_q(q + nq_o, nq_d, &gd);
+    if (st != SAS_OK) return st;
+    float* tabd = reinterpret_cast<float*>(w + L.tabd);
+    SAS_HIP(sas::launch_copy_cols(table, t, nq, nq_o, nq_d, nq_d, tabd, hd));
+    const Schedule sd = type_schedule(ctx, std::vector<int64_t>{n}, t, nq_d, q[nq - 1], !gd.uniform || ctx->force_direct,
+                                      use_per_atom(ctx, t, n), 0, kBinPoolHybrid);
+    const Layout Ld = make_layout(sd, t, nq_d);
+    void* wd = w + L.direct;
+    st = stage_upload(ctx, wd, Ld, upload_image(sd, Ld, gd), hd);
+    if (st != SAS_OK) return st;
+    st = enqueue_forward(ctx, sd, Ld, coords, types, tabd, t, nq_d, gd.q0, gd.dq, I_out + nq_o, wd, hd);
+    if (st != SAS_OK) return st;
   }
   if (n_orient) *n_orient = nq_o;
   return SAS_OK;
