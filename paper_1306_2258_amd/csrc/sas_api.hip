@@ -1504,6 +1504,7 @@ sas_status sas_plan_execute(sas_plan* p, void* stream) {
     const bool forced = p->ctx->force_bj > 0 || p->ctx->force_qc > 0;
     auto it = p->ctx->tuned.find(key);
     if (p->sc.bins) {
+      // (nothing to choose)
     } else if (forced) {
       tile.bj = p->ctx->force_bj;
       tile.persist = p->ctx->launch != 2 && !p->direct && !p->per_atom;

@@ -79,9 +79,12 @@ constexpr int kAdjPaBJ = 128; // J-block atoms of the per-atom adjoint, at most
 // own: kPaWaves, one per wave of a work-group, where the strips alone would
 // leave the chip idle or its last round nearly empty.  A structure's parts
 // depend on it and the tile shape alone (not on its batch), so a forced shape
-// reproduces a call's bits.
+// reproduces a call's bits.  Adjoint and profile in us, 100 q, one wave against
+// four: 3,000 atoms (576 strips of 128) 240, 142 against 147, 75; 6,000 (2,256) 525,
+// 237 against 406, 201; 7,500 656, 343 against 621, 298; 9,000 (5,111) 880, 415
+// against 879, 422; 11,000 1,268, 593 against 1,306, 615.
 constexpr int kPaWaves = 4;
-constexpr int64_t kPaFewStrips = 8192;
+constexpr int64_t kPaFewStrips = 5120;
 
 struct AdjArgs {
   DescView sd;          // one structure

@@ -64,8 +64,8 @@ def test_parts_of_one_molecule(sd, n, nq, grid):
     assert np.linalg.norm(t - ref) <= GTOL * np.linalg.norm(ref)
 
 
-# 8,192 strips of 128 atoms: about 11,500 atoms; sampled q
-@pytest.mark.parametrize("n", [11400, 11700])
+# 5,120 strips of 128 atoms lie between the first two; sampled q
+@pytest.mark.parametrize("n", [9000, 9200, 11400, 11700])
 def test_where_the_parts_end(sd, n):
     print(f"[case] per-atom N={n}", flush=True)
     m = W.with_per_atom_factors(W.random_molecule(9200, n, 16, q1=0.6, extent=60.0), 9300)
