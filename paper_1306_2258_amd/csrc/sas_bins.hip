@@ -106,8 +106,9 @@ __device__ __forceinline__ void empty_bins(unsigned long long* h, const BinSeg* 
 
 // The squared distances come from the matrix cores: s = |x_j|^2 - 2 x_i x_j +
 // |x_i|^2 is a product of depth four, [x_j, |x_j|^2] by [-2 x_i, 1], plus a
-// constant per i.  v_mfma_f64_4x4x4 makes 64 of them in 16 cycles beside the
-// vector pipes, which would take seven FP64 instructions for each.  The
+// constant per i.  v_mfma_f64_4x4x4 makes 64 of them in 16 cycles; the vector
+// pipes, with the same FP64 rate, take as long (the rod 1.81 and 1.82 ms), but
+// the gradient's sums are such products too.  The
 // coordinates are centred, so the cancellation leaves s good to about 1e-9 in
 // units of a bin's width squared, at any distance.
 // Lane l holds the pair of atom i0 + l % 16 (16 lane-side atoms per product)
@@ -207,6 +208,14 @@ __device__ __forceinline__ void sweep(const double* __restrict__ xs, int64_t ld,
   }
 }
 
+// Bound by VALU issue (24 instructions per pair) and the three LDS additions,
+// which overlap little: without the additions the 50,000-atom rod takes 1.07 to
+// 1.14 ms of 1.75.  One work-group per CU owns all of its LDS, so that a window
+// covers 3,400 A at q = 1 and most molecules fit one; an equal share of the items
+// each keeps the CUs level without a counter.  Copies of a bin for consecutive
+// lanes spread the banks (additions 11.7 -> 4 cycles per wave instruction with 16);
+// each copy costs its emptying, hence the limit by pairs.  The same 1.25e9 pairs
+// and 200 q by the recurrence: 13.9 ms; 10,000 atoms, 100 q: 0.34 -> 0.06.
 __global__ __launch_bounds__(kBinThreads) void k_bins(BinArgs b) {
   __shared__ unsigned long long h[(kBinCap + kWave) * 3];
   __shared__ BinSeg seg[kBinSegs];
@@ -424,6 +433,8 @@ __device__ __forceinline__ double sinc_slope(double x, double ix) {
 
 // One work-group (four waves): kFieldBins bins, TPG type pairs from
 // blockIdx.y * TPG.  The lanes hold the nodes, the waves take every fourth q.
+// Bound by the FP64 sine and cosine per node and q, which all type pairs share; 8 us
+// of the 20,000-atom gradient's 460.
 template <int TPG>
 __global__ __launch_bounds__(256) void k_bins_field(BinArgs b, const float* __restrict__ table,
                                                     const double* __restrict__ w, int32_t Nq, double q0, double dq,
@@ -557,6 +568,11 @@ __device__ __forceinline__ void sweep_grad(const double* __restrict__ xs, int64_
   }
 }
 
+// Every ordered pair once (an unordered sweep would need a reduction over lanes per
+// swept atom).  Bound by VALU issue and the gather of a pair's six coefficients
+// (three 8-byte LDS reads at random bins; the copies of a table spread them as in
+// k_bins).  20,000 atoms, 4e8 ordered pairs: 441 us, where the adjoint recurrence
+// takes 2.3 ms at 100 q.
 __global__ __launch_bounds__(kBinThreads) void k_bins_grad(BinArgs b) {
   __shared__ float2 h[kBinCap * 3];
   __shared__ int32_t below;
@@ -803,6 +819,8 @@ __device__ void bins_sum(const BinArgs& b, int s, int first, const float* __rest
     __hip_atomic_store(b.part + static_cast<int64_t>(s) * Nq + m, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Bound by the FP64 sine of every node and q, and in small calls by latency (12 us at
+// 1,000 atoms, 52 us for the rod's 6,541 bins x 200 q x 15 type pairs).
 // The last of a structure's work-groups to finish (a count per structure and q
 // group) also forms the profile, which spares a kernel: the others' rows are
 // stored and read past the XCDs' own caches.
